@@ -201,11 +201,14 @@ apx_status apx_set_lean_scan(apx_ctx *ctx, int enable);
  * the reduction.  Diagnostic only. */
 apx_status apx_last_lean_rescans(apx_ctx *ctx, int32_t *rows);
 
-/* apx_set_graphs -- replay the iteration loop of ap_solve as a captured HIP
- * graph (enable = 1, the default; the environment variable APX_GRAPHS=0
- * turns it off at context creation) or launch every kernel from the host
- * (enable = 0).  The graph runs on a private stream of the context, ordered
- * after the context stream with an event; results are identical either way. */
+/* apx_set_graphs -- run the iteration loop of ap_solve without the host
+ * launching its kernels one by one (enable = 1, the default; the environment
+ * variable APX_GRAPHS=0 turns it off at context creation): explicit messages
+ * of up to 3072 points in one cooperative launch that holds them in
+ * registers, other runs as a captured HIP graph, replayed on a private
+ * stream of the context that is ordered after the context stream with an
+ * event.  enable = 0 launches every kernel from the host.  Results are
+ * identical either way. */
 apx_status apx_set_graphs(apx_ctx *ctx, int enable);
 
 /* ---------------------------------------------------------------------------

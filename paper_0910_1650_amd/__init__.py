@@ -401,7 +401,7 @@ def apx_last_lean_rescans(device=None) -> int:
 
 
 def apx_set_graphs(enable: bool, device=None) -> None:
-    """Replay ap_solve's iteration loop as a captured HIP graph (default) or not."""
+    """Run ap_solve's iteration loop in one launch or a captured HIP graph (default), or launch by launch."""
     ctx = context(device)
     _check(ctx, lib().apx_set_graphs(ctx, int(bool(enable))), "apx_set_graphs")
 

@@ -352,6 +352,98 @@ apx_status graph_chunk(apx_ctx *ctx, const PassPlan &pl, int mode, const float *
 
 }  // namespace
 
+namespace {
+
+// Rows a workgroup of the one-launch solve owns at most, one per wavefront.
+// Up to 1024 points eight, so that fewer wavefronts share a SIMD (at n = 1000
+// 6.0 us per iteration against 6.7 with twelve, at n = 300 4.7 against 5.0;
+// with four or fewer the exchange between more workgroups costs more, 7.6 at
+// n = 1000); above, all twelve are needed or make no difference (n = 2000:
+// 8.7 and 8.8).
+int res_rows(int64_t n) { return n <= 1024 ? 8 : 12; }
+
+// ap_solve in one launch (resident.hip) on the workspace w; APX_ENOTIMPL
+// (nothing written) where the size does not fit or the run did not end.
+apx_status resident_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *R, float *A, int32_t warm,
+                          const apx_params *params, int32_t *idx, const IterWs &w, apx_result *res) {
+    ResPlan pl{};
+    if (!res_plan(n, ctx->num_cus, res_rows(n), &pl)) return APX_ENOTIMPL;
+    // the exchange words (16 n bytes per member and a little) take the place
+    // of the exception lists (16 KB per row)
+    if (pl.words * 8 > 2 * w.xstride) return APX_ENOTIMPL;
+    hipStream_t s = ctx->stream;
+    ResInst d{};
+    d.S = S;
+    d.R = R;
+    d.A = A;
+    d.ld = ld;
+    d.n = (int32_t)n;
+    d.load_a = warm != APX_COLD;
+    d.load_r = warm == APX_WARM_AR;
+    d.idx = idx;
+    d.eflag = w.eflag;
+    ResOut *out = reinterpret_cast<ResOut *>(static_cast<char *>(ctx->pinned) + 3072);
+    d.out = out;
+    res_exchange(pl, n, w.xst, &d);
+    out->done = 0;
+    const float lam = params->damping;
+    HIP_TRY(launch_res_zero(w.xst, pl.words, s), "exchange words");
+    // a column-structured A_0 takes the undamped first step (damping 0 on R = 0)
+    const hipError_t e = launch_resident(pl, d, lam, warm == APX_WARM_COLUMNS ? 0.0f : lam, params->max_iter,
+                                         params->conv_iter, s);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return APX_ENOTIMPL;
+    }
+    HIP_TRY(hipStreamSynchronize(s), "sync");
+    if (!out->done) {
+        // a wait was given up: a cold start can begin again, a warm start may
+        // have lost its A_0 and R_0 to the rows already written
+        return warm == APX_COLD ? APX_ENOTIMPL
+                                : set_err(ctx, APX_EDEVICE, "a wait between workgroups timed out");
+    }
+    ctx->last_imp_iters = ctx->last_ia_iters = 0;
+    ctx->last_exp_iters = out->iterations;
+    ctx->last_fallback = 0;
+    ctx->last_lean_rescans = 0;
+    res->iterations = out->iterations;
+    res->converged = out->converged;
+    res->n_exemplars = out->n_exemplars;
+    double dp = out->dpsim, ep = out->expref;
+    if (params->flags & APX_RAW_LABELS) {
+        // d_T = argmax_k a_T(i,k) + r_T(i,k) from the messages just returned
+        HIP_TRY(launch_decide(A, R, n, ld, w.dec, s), "decisions");
+        FinalArgs fa{};
+        fa.S = S;
+        fa.ld = ld;
+        fa.n = (int32_t)n;
+        fa.eflag = w.eflag;
+        fa.ex = w.ex;
+        fa.nex = w.nex;
+        fa.idx = idx;
+        fa.contrib = w.contrib;
+        fa.sums = w.sums;
+        fa.raw = w.dec;
+        HIP_TRY(launch_finalize(fa, s), "finalize");
+        double *hd = reinterpret_cast<double *>(static_cast<char *>(ctx->pinned) + 256);
+        HIP_TRY(hipMemcpyAsync(hd, w.sums, 2 * sizeof(double), hipMemcpyDeviceToHost, s), "sums");
+        HIP_TRY(hipStreamSynchronize(s), "sync");
+        dp = hd[0];
+        ep = hd[1];
+    }
+    if (res->n_exemplars == 0) {
+        res->dpsim = res->expref = res->netsim = NAN;
+    } else {
+        res->dpsim = dp;
+        res->expref = ep;
+        res->netsim = dp + ep;
+    }
+    res->status = APX_OK;
+    return APX_OK;
+}
+
+}  // namespace
+
 namespace apx {
 apx_status check_iterate(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, const float *R, const float *A,
                          float damping, int32_t n_iter) {
@@ -681,10 +773,6 @@ apx_status ap_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *
     IterWs w{};
     APX_TRY(iter_ws(ctx, n, ld, true, pl, w));
     const bool cols = warm == APX_WARM_COLUMNS;
-    HIP_TRY(launch_state_init(w.st, params->max_iter, params->conv_iter, lam, s, msg_rule ? 1 : 0,
-                              params->msg_tol, cols ? 1 : 0), "state init");
-    HIP_TRY(launch_fill_u8(w.eflag, n, 0, s), "flags");
-
     // R_t lives in buf[t & 1]; buf[0] is the caller's R.  With R_0 = 0 (cold
     // start or A_0 only) R is kept implicitly (ImpArgs) unless disabled.
     float *buf[2] = {R, w.R2};
@@ -711,6 +799,17 @@ apx_status ap_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *
         imp_a = r_ok && ia_start && ctx->implicit_a > 0 && ia_plan(n, ctx->num_cus, &apl);
         implicit = r_ok;
     }
+    // Explicit messages that fit in the register files: the whole run in one
+    // launch.  It writes R and A only at its end, so a run that did not end
+    // (a wait between its workgroups given up) goes on to the passes below.
+    if (!implicit && !msg_rule && ctx->graphs && !ctx->prof) {
+        const apx_status rs = resident_solve(ctx, S, n, ld, R, A, warm, params, idx, w, res);
+        if (rs != APX_ENOTIMPL) return rs;
+    }
+    HIP_TRY(launch_state_init(w.st, params->max_iter, params->conv_iter, lam, s, msg_rule ? 1 : 0,
+                              params->msg_tol, cols ? 1 : 0), "state init");
+    HIP_TRY(launch_fill_u8(w.eflag, n, 0, s), "flags");
+
     // the implicit-A passes of this solve read A' through its blocks
     struct BlkGuard {
         apx_ctx *c;

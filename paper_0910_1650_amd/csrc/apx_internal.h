@@ -230,6 +230,37 @@ hipError_t launch_extract_diag(const float *A, int64_t ld, int32_t n, float *adi
 // Clears the frozen and overflow flags after an overflow hand-over.
 hipError_t launch_state_resume(ApState *st, hipStream_t s);
 
+// The whole solve in one launch, messages in registers (resident.hip).
+constexpr int64_t kResMaxN = 3072;
+struct ResOut {
+    double dpsim, expref;
+    int32_t iterations, converged, n_exemplars;
+    int32_t done;        // 1 when the run ended by its stop rule
+};
+struct ResInst {
+    const float *S;
+    float *R, *A;        // outputs; A_0, R_0 on entry where load_a, load_r
+    int64_t ld;
+    int32_t n, members, groups, gpm, variant;
+    int32_t load_a, load_r;
+    unsigned long long *part, *pair, *stat;   // exchange words, zero at the start
+    int32_t *idx;
+    uint8_t *eflag;
+    ResOut *out;
+};
+struct ResPlan {
+    int ej, rpw, groups, gpm, members, rows;
+    size_t lds;
+    int64_t words;       // 8-byte exchange words
+};
+// Plan with at most max_rows rows per member; false when n does not fit.
+bool res_plan(int64_t n, int num_cus, int max_rows, ResPlan *pl);
+// Carves the exchange words of an instance from mem (pl.words words).
+void res_exchange(const ResPlan &pl, int64_t n, void *mem, ResInst *d);
+hipError_t launch_res_zero(void *mem, int64_t words, hipStream_t s);
+hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,
+                           int32_t conv_iter, hipStream_t s);
+
 // Finalize: labels and FP64 dpsim / expref.
 struct FinalArgs {
     const float *S;
