@@ -257,8 +257,9 @@ apx_status apx_tune_set_form(apx_ctx *ctx, int64_t n, int32_t form);
 /* apx_tune_get_form -- the form recorded for n (APX_FORM_DEFAULT if none)
  * and, if ms is non-null, the 3 measured ms per iteration (0 if not timed). */
 apx_status apx_tune_get_form(apx_ctx *ctx, int64_t n, int32_t *form, double *ms);
-/* apx_autotune_batched -- time the plans of the persistent batched launch
- * (ap_solve_batched, pap_solve's Step 2) for a batch of `count` instances of
+/* apx_autotune_batched -- time the plans of the streaming batched launch
+ * (instances above 3072 points of ap_solve_batched, pap_solve's Step 2) for a
+ * batch of `count` instances of
  * sizes[j] points (host) on scratch instances of those sizes (allocated and
  * freed: 3 n x n matrices each), over workgroups per compute unit 1..4 and
  * 2, 8 or 32 rows at least per team member, and keep the fastest for
@@ -433,13 +434,17 @@ typedef struct {
 
 /*
  * ap_solve_batched -- Algorithm 1 on `count` independent instances of uneven
- * size (inst: host array) in one persistent cooperative launch: each
- * instance gets a team of workgroups (sized in proportion to its n^2; with
- * more instances than workgroups, instances are dealt to single workgroups
- * largest first), teams meet at device-side barriers, and each instance
- * keeps its own stop rule and stops independently.  Per instance the arithmetic is that of ap_solve;
- * only the grouping of the FP32 column partial sums differs (rows are split
- * into blocks differently), so results agree with ap_solve to rounding.
+ * size (inst: host array).  Instances of up to 3072 points run in one
+ * cooperative launch per class of sizes (up to 1024 points, above) with their
+ * messages in registers: an instance gets as many workgroups as its rows
+ * need, all instances run at once where they fit the chip, else in turns
+ * largest first; their results are those of ap_solve with explicit messages,
+ * bit for bit.  Larger instances (and all, while APX_BATCH_WPC or
+ * APX_BATCH_MIN_ROWS is set) run in a second persistent cooperative launch
+ * that streams R and A: each gets a team of workgroups in proportion to its
+ * n^2, and only the grouping of the FP32 column partial sums differs from
+ * ap_solve (rows are split into blocks differently), so results agree with
+ * ap_solve to rounding.  Each instance keeps its own stop rule.
  * The results are deterministic.  res (host, count).  Instances need
  * 2 <= n <= 12288.  Synchronises.
  */

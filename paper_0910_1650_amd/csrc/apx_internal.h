@@ -253,8 +253,19 @@ struct ResPlan {
     size_t lds;
     int64_t words;       // 8-byte exchange words
 };
+constexpr int kResWaves = 12;   // wavefronts of a workgroup (a member)
 // Plan with at most max_rows rows per member; false when n does not fit.
 bool res_plan(int64_t n, int num_cus, int max_rows, ResPlan *pl);
+// Most rows a member can own at n points (the widest variant).
+int res_max_rows(int64_t n);
+struct ResTask {
+    int32_t inst, rank;
+};
+// A batch holds instances of one class only (res_small or not).
+bool res_small(int64_t n);
+hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
+                                 const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
+                                 int32_t conv_iter, hipStream_t s);
 // Carves the exchange words of an instance from mem (pl.words words).
 void res_exchange(const ResPlan &pl, int64_t n, void *mem, ResInst *d);
 hipError_t launch_res_zero(void *mem, int64_t words, hipStream_t s);

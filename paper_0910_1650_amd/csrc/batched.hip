@@ -1,8 +1,12 @@
-// batched.hip -- many independent AP instances of uneven size in ONE
-// persistent launch (Algorithm 1 run on each instance; the sub-problems of
-// partition AP, Algorithm 2 Step 2, are such a batch).
+// batched.hip -- many independent AP instances of uneven size at once
+// (Algorithm 1 run on each instance; the sub-problems of partition AP,
+// Algorithm 2 Step 2, are such a batch).
 //
-// The launch is a fixed grid of workgroups that are all resident at once (a
+// Instances of up to kResMaxN points go to the one-launch solve with messages
+// in registers (resident.hip): 64 instances of 100 to 1000 points (64-D) take
+// 3.2 ms so, 37 ms in the streaming launch below, whose teams flush the L2s
+// four times per iteration at their barriers.  The streaming launch keeps the
+// larger instances.  It is a fixed grid of workgroups that are all resident at once (a
 // cooperative launch).  The host cuts the grid into teams over a ragged
 // table: an instance gets a team of g workgroups in proportion to its n^2
 // (member r owns a contiguous block of rows and the same block of columns
@@ -681,17 +685,211 @@ BatchPlan make_plan(int32_t count, const BatchSpec *spec, int num_cus, int wpc, 
 
 }  // namespace
 
+namespace {
+
+// Instances of up to kResMaxN points: the one-launch solve with messages in
+// registers (resident.hip), many instances to a launch.
+struct ResBatch {
+    std::vector<int32_t> order;    // instances, largest first
+    std::vector<ResPlan> plan;     // by position in `order`
+    std::vector<ResTask> tasks;
+    std::vector<int32_t> lane;     // grid + 1 entries
+    std::vector<size_t> o_x, o_e;  // exchange words (relative to o_x0), flags
+    bool small = false;            // res_small of all of them
+    int grid = 0;
+    size_t lds = 0;
+    size_t o_tab, tab_bytes, o_task, o_lane, o_x0, x_bytes, o_out, o_abort, bytes;
+};
+
+// Few rows per member where the members of all instances then fit the chip
+// at once (an iteration is four microseconds of exchange and 0.6 per chunk
+// of four columns and row of a wavefront); else the most rows a member can
+// hold, so that the instances take the fewest turns.
+bool res_batch_plan(const BatchSpec *spec, const std::vector<int32_t> &order, int num_cus, ResBatch *B) {
+    if (order.empty()) return false;
+    B->small = res_small(spec[order[0]].n);
+    B->order = order;
+    B->plan.resize(order.size());
+    for (int rpw = 1; rpw <= 8; ++rpw) {
+        const int lv = rpw * kResWaves;
+        int64_t sum = 0;
+        for (size_t q = 0; q < order.size(); ++q) {
+            const int64_t n = spec[order[q]].n;
+            const int most = res_max_rows(n);
+            if (!res_plan(n, num_cus, lv < most ? lv : most, &B->plan[q]) &&
+                !res_plan(n, num_cus, most, &B->plan[q]))
+                return false;
+            sum += B->plan[q].members;
+        }
+        if (sum <= num_cus) break;
+    }
+    // each instance, largest first, to the workgroups that are free soonest
+    std::vector<std::pair<float, int>> load(num_cus);
+    for (int b = 0; b < num_cus; ++b) load[b] = {0.0f, b};
+    std::vector<std::vector<ResTask>> per(num_cus);
+    for (size_t q = 0; q < order.size(); ++q) {
+        const ResPlan &p = B->plan[q];
+        if (p.members < num_cus) std::nth_element(load.begin(), load.begin() + p.members, load.end());
+        float start = 0.0f;
+        for (int m = 0; m < p.members; ++m) start = load[m].first > start ? load[m].first : start;
+        const float end = start + 4.0f + 0.6f * (float)(p.ej * p.rpw);
+        for (int m = 0; m < p.members; ++m) {
+            load[m].first = end;
+            per[load[m].second].push_back(ResTask{(int32_t)q, m});
+        }
+        B->lds = p.lds > B->lds ? p.lds : B->lds;
+    }
+    B->lane.push_back(0);
+    for (int b = 0; b < num_cus; ++b)
+        if (!per[b].empty()) {
+            B->tasks.insert(B->tasks.end(), per[b].begin(), per[b].end());
+            B->lane.push_back((int32_t)B->tasks.size());
+            ++B->grid;
+        }
+    WsLayout L;
+    B->o_tab = L.take(sizeof(ResInst) * order.size());
+    B->o_task = L.take(sizeof(ResTask) * B->tasks.size());
+    B->o_lane = L.take(sizeof(int32_t) * B->lane.size());
+    B->tab_bytes = L.off;
+    B->o_out = L.take(sizeof(ResOut) * order.size());
+    B->o_abort = L.take(8);
+    B->o_x0 = L.off;
+    for (const ResPlan &p : B->plan) B->o_x.push_back(L.take(8 * (size_t)p.words));
+    B->x_bytes = L.off - B->o_x0;
+    for (int32_t j : order) B->o_e.push_back(L.take((size_t)spec[j].n));
+    B->bytes = L.off;
+    return true;
+}
+
+// The instances of one class (res_small or not), largest first.
+std::vector<int32_t> res_order(int32_t count, const BatchSpec *spec, bool small) {
+    std::vector<int32_t> order;
+    for (int32_t j = 0; j < count; ++j)
+        if (spec[j].n <= kResMaxN && res_small(spec[j].n) == small) order.push_back(j);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return spec[x].n > spec[y].n; });
+    return order;
+}
+
+// Solves the instances of the plan; results by instance number.
+apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spec, int32_t warm,
+                           const apx_params *params, apx_result *res) {
+    hipStream_t s = ctx->stream;
+    char *b = static_cast<char *>(ctx->ws) + ctx->ws_base;
+    const size_t cnt = B.order.size();
+    std::vector<char> tab(B.tab_bytes, 0);
+    ResInst *inst = reinterpret_cast<ResInst *>(tab.data() + B.o_tab);
+    for (size_t q = 0; q < cnt; ++q) {
+        const BatchSpec &sp = spec[B.order[q]];
+        ResInst &d = inst[q];
+        d.S = sp.S;
+        d.R = sp.R;
+        d.A = sp.A;
+        d.ld = sp.ld;
+        d.n = (int32_t)sp.n;
+        d.load_a = warm != APX_COLD;
+        d.load_r = warm == APX_WARM_AR;
+        d.idx = sp.idx;
+        d.eflag = reinterpret_cast<uint8_t *>(b + B.o_e[q]);
+        d.out = reinterpret_cast<ResOut *>(b + B.o_out) + q;
+        res_exchange(B.plan[q], sp.n, b + B.o_x[q], &d);
+    }
+    std::memcpy(tab.data() + B.o_task, B.tasks.data(), sizeof(ResTask) * B.tasks.size());
+    std::memcpy(tab.data() + B.o_lane, B.lane.data(), sizeof(int32_t) * B.lane.size());
+    // the results and the exchange words start at zero
+    hipError_t e;
+    std::vector<ResOut> out(cnt);
+    if ((e = hipMemcpyAsync(b, tab.data(), B.tab_bytes, hipMemcpyHostToDevice, s)) ||
+        (e = launch_res_zero(b + B.o_out, (int64_t)((B.o_x0 - B.o_out + B.x_bytes) / 8), s)) ||
+        (e = launch_resident_batch(B.small, B.grid, B.lds, reinterpret_cast<const ResInst *>(b + B.o_tab),
+                                   reinterpret_cast<const ResTask *>(b + B.o_task),
+                                   reinterpret_cast<const int32_t *>(b + B.o_lane),
+                                   reinterpret_cast<unsigned long long *>(b + B.o_abort), params->damping,
+                                   params->max_iter, params->conv_iter, s)) ||
+        (e = hipMemcpyAsync(out.data(), b + B.o_out, sizeof(ResOut) * cnt, hipMemcpyDeviceToHost, s)) ||
+        (e = hipStreamSynchronize(s)))
+        return hip_err(ctx, e, "batched launch");
+    for (size_t q = 0; q < cnt; ++q) {
+        const ResOut &o = out[q];
+        if (!o.done) return set_err(ctx, APX_EDEVICE, "batched launch: a wait between workgroups timed out");
+        apx_result &r = res[B.order[q]];
+        std::memset(&r, 0, sizeof r);
+        r.iterations = o.iterations;
+        r.converged = o.converged;
+        r.n_exemplars = o.n_exemplars;
+        if (o.n_exemplars == 0) {
+            r.dpsim = r.expref = r.netsim = NAN;
+        } else {
+            r.dpsim = o.dpsim;
+            r.expref = o.expref;
+            r.netsim = o.dpsim + o.expref;
+        }
+        r.status = APX_OK;
+    }
+    return APX_OK;
+}
+
+}  // namespace
+
 size_t batched_ws_bytes(int32_t count, const BatchSpec *spec, int num_cus) {
     // an upper bound: the plan at the largest workgroups per CU and the
     // largest teams (one row per member at least)
-    return make_plan(count, spec, num_cus, kMaxWpc, 1).bytes;
+    size_t bytes = make_plan(count, spec, num_cus, kMaxWpc, 1).bytes;
+    for (bool small : {false, true}) {
+        ResBatch B;
+        if (res_batch_plan(spec, res_order(count, spec, small), num_cus, &B) && B.bytes > bytes) bytes = B.bytes;
+    }
+    return bytes;
 }
 
+namespace {
+// The streaming batch: tables, initial state, one persistent cooperative
+// launch, then R_T and the labels.
+apx_status batched_stream(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int32_t warm, const apx_params *params,
+                          apx_result *res);
+}  // namespace
+
 // Host driver shared by ap_solve_batched and pap_solve (Step 2): the
-// workspace slice starts at ctx->ws_base.  Tables, initial state, one
-// persistent cooperative launch, then R_T and the labels.
+// workspace slice starts at ctx->ws_base.
 apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int32_t warm,
                          const apx_params *params, apx_result *res) {
+    int64_t max_n = 0;
+    for (int j = 0; j < count; ++j) max_n = spec[j].n > max_n ? spec[j].n : max_n;
+    if (max_n > 12 * 4 * BT)
+        return set_err(ctx, APX_ENOTIMPL, "batched instances are limited to n <= %d", 12 * 4 * BT);
+    // Instances whose messages fit in registers go first, one launch for each
+    // class of sizes; a forced or hand-set plan of the launch below (the tuner,
+    // APX_BATCH_WPC, APX_BATCH_MIN_ROWS) keeps every instance there.
+    const bool streamed = ctx->force_bwpc || ctx->force_bmin || getenv("APX_BATCH_WPC") || getenv("APX_BATCH_MIN_ROWS");
+    std::vector<char> done(count, 0);
+    int32_t left = count;
+    for (bool small : {false, true}) {
+        ResBatch B;
+        if (streamed || !res_batch_plan(spec, res_order(count, spec, small), ctx->num_cus, &B)) continue;
+        if (ctx->ws_external && ctx->ws_base + B.bytes > ctx->ws_bytes) continue;
+        apx_status st = ws_reserve(ctx, ctx->ws_base + B.bytes);
+        if (st == APX_OK) st = res_batch_solve(ctx, B, spec, warm, params, res);
+        if (st != APX_OK) return st;
+        for (int32_t j : B.order) done[j] = 1;
+        left -= (int32_t)B.order.size();
+    }
+    if (left == 0) return APX_OK;
+    if (left < count) {
+        std::vector<BatchSpec> rest;
+        for (int32_t j = 0; j < count; ++j)
+            if (!done[j]) rest.push_back(spec[j]);
+        std::vector<apx_result> rr(rest.size());
+        const apx_status st = batched_stream(ctx, left, rest.data(), warm, params, rr.data());
+        if (st == APX_OK)
+            for (int32_t j = 0, q = 0; j < count; ++j)
+                if (!done[j]) res[j] = rr[q++];
+        return st;
+    }
+    return batched_stream(ctx, count, spec, warm, params, res);
+}
+
+namespace {
+apx_status batched_stream(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int32_t warm, const apx_params *params,
+                          apx_result *res) {
     hipStream_t s = ctx->stream;
     int64_t max_n = 0;
     for (int j = 0; j < count; ++j) max_n = spec[j].n > max_n ? spec[j].n : max_n;
@@ -803,6 +1001,7 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
     }
     return APX_OK;
 }
+}  // namespace
 
 }  // namespace apx
 

@@ -41,18 +41,29 @@ namespace {
 
 constexpr float kNegInf = -INFINITY;
 // (chunks, rows per wavefront) instantiated; the register file holds 12
-// chunks of three matrices per lane.
-#define APX_RES_VARIANTS(X)                                                                                     \
-    X(1, 1) X(1, 2) X(1, 4) X(1, 8) X(2, 1) X(2, 2) X(2, 4) X(3, 1) X(3, 3) X(4, 1) X(4, 2) X(5, 1) X(5, 2)       \
-    X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1)
+// chunks of three matrices per lane.  A batch launches the sets SMALL and
+// LARGE apart: one kernel with all of them spilled 228 registers.
+#define APX_RES_SMALL(X) \
+    X(1, 1) X(1, 2) X(1, 3) X(1, 5) X(2, 1) X(2, 2) X(2, 3) X(3, 1) X(3, 2) X(4, 1) X(4, 2)
+#define APX_RES_LARGE(X) X(5, 1) X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1)
+#define APX_RES_VARIANTS(X) APX_RES_SMALL(X) APX_RES_LARGE(X)
+constexpr int kSmallChunks = 4;
 
-constexpr int RW = 12;            // wavefronts per workgroup (3 per SIMD: 168 registers)
+constexpr int RW = kResWaves;     // wavefronts per workgroup (3 per SIMD: 168 registers)
 constexpr int RT = 64 * RW;
+// Up to 1536 points (groups of at most three rows) a column sum reads four
+// rows at once and looks up the ends of groups in a mask (the sum of 24 rows
+// at n = 750 3780 -> 2500 cycles); longer groups are summed one by one (n =
+// 3001: 13.5 us per iteration, 14.8 with the mask).
+constexpr int kSmallGroups = 6;
 constexpr int kRedLanes = 8;      // lanes that finish one column's sum
-constexpr int kMaxRows = RT / kRedLanes;   // rows a member can own
+constexpr int kMaxRows = 64;      // rows a member can own (one bit each, kRedLanes threads each)
+static_assert(kMaxRows * kRedLanes <= RT, "threads of the reduction");
 // polls of one word before a wait is given up (each takes about a
 // microsecond; a legitimate wait is one iteration of another member)
 constexpr uint32_t kPollLimit = 1u << 21;
+
+constexpr uint32_t kArriveLimit = 1u << 28;
 
 typedef unsigned long long u64;
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -159,15 +170,12 @@ struct ResLds {
     int *fail;
 };
 
-struct ResTask {
-    int32_t inst, rank;
-};
-
 struct ResArgs {
-    ResInst one;              // the instance, when insts is null (workgroup = member)
-    const ResInst *insts;
+    ResInst one;              // the instance of a single solve (workgroup = member)
+    const ResInst *insts;     // a batch's instances
     const ResTask *tasks;     // workgroup b runs tasks [lane[b], lane[b+1]) in order
     const int32_t *lane;
+    u64 *abort;               // set when a wait of a batch was given up
     float lam, lam0;          // damping; damping of the first responsibility step
     int32_t max_iter, conv_iter;
 };
@@ -276,6 +284,8 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         }
     }
     const int64_t pstride = (int64_t)n * M;
+    u64 ends = 0ull;       // bit r: row r of the block is the last of its group
+    for (int g = g0; g < g1; ++g) ends |= 1ull << (group_row(g + 1, n, G) - row0 - 1);
     const int slices = RT / rows;
     int rsc = (tid / rows) << 16 | (tid % rows);   // slice and column of this thread in exchange 1
 
@@ -462,12 +472,30 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
                 const int kp = tid + u * RT, k = h * PC + kp;
                 if (kp < PC && k < n) {
                     double tot = 0.0;
-                    int lr = 0;
-                    for (int g = g0; g < g1; ++g) {
-                        const int end = group_row(g + 1, n, G) - row0;
+                    if constexpr (EJ <= kSmallGroups) {
+                        // groups of one to three rows: four rows in flight
                         float acc = 0.0f;
-                        for (; lr < end; ++lr) acc += L.pos[lr * PC + kp];
-                        tot += (double)acc;
+                        for (int lr = 0; lr < rows; lr += 4) {
+                            float v[4];
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) v[x] = L.pos[(lr + x < rows ? lr + x : lr) * PC + kp];
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) {
+                                if (lr + x < rows) acc += v[x];
+                                if ((ends >> (lr + x)) & 1ull) {
+                                    tot += (double)acc;
+                                    acc = 0.0f;
+                                }
+                            }
+                        }
+                    } else {
+                        int lr = 0;
+                        for (int g = g0; g < g1; ++g) {
+                            const int end = group_row(g + 1, n, G) - row0;
+                            float acc = 0.0f;
+                            for (; lr < end; ++lr) acc += L.pos[lr * PC + kp];
+                            tot += (double)acc;
+                        }
                     }
                     if (M > 1) {
                         st_dev(part, poff[h][u], ((u64)__double_as_longlong(tot) & 0x7FFFFFFFFFFFFFFFull) | sign);
@@ -726,6 +754,65 @@ __global__ __launch_bounds__(RT) void k_resident(ResArgs p) {
     (void)res_run<EJ, RPW>(p.one, blockIdx.x, p, lds);
 }
 
+// Waits until every member of the instance has come to it (the others may
+// still be at work on earlier instances, for as long as those run), or until
+// a wait has been given up somewhere.
+__device__ __forceinline__ bool all_arrived(const ResInst &d, int rank, const u64 *abort, char *lds) {
+    int *stop = reinterpret_cast<int *>(lds);
+    if (threadIdx.x == 0) {
+        *stop = 0;
+        st_dev(d.stat + rank, ~0ull);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < d.members) {
+        uint32_t polls = 0u;
+        while (ld_dev(d.stat + threadIdx.x) == 0ull) {
+            __builtin_amdgcn_s_sleep(8);
+            if (ld_dev(abort) != 0ull || ++polls > kArriveLimit) {
+                *stop = 1;
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    const bool ok = *stop == 0;
+    __syncthreads();
+    return ok;
+}
+
+// Many instances of uneven size: workgroup b runs its tasks in turn.  The
+// tasks of every workgroup are in one order of the instances, so the first
+// instance not yet done always has all of its members at work on it.
+template <bool SMALL>
+__global__ __launch_bounds__(RT) void k_resident_batch(ResArgs p) {
+    extern __shared__ char lds[];
+    const int q1 = p.lane[blockIdx.x + 1];
+    for (int q = p.lane[blockIdx.x]; q < q1; ++q) {
+        const ResTask tk = p.tasks[q];
+        const ResInst d = p.insts[tk.inst];
+        bool ok = false;
+        if (d.members > 1 && !all_arrived(d, tk.rank, p.abort, lds)) return;
+#define APX_RES_CASE(e, w) case e * 16 + w: ok = res_run<e, w>(d, tk.rank, p, lds); break;
+        if constexpr (SMALL) {
+            switch (d.variant) {
+                APX_RES_SMALL(APX_RES_CASE)
+            default: break;
+            }
+        } else {
+            switch (d.variant) {
+                APX_RES_LARGE(APX_RES_CASE)
+            default: break;
+            }
+        }
+#undef APX_RES_CASE
+        if (!ok) {
+            if (threadIdx.x == 0) st_dev(p.abort, 1ull);
+            return;
+        }
+        __syncthreads();
+    }
+}
+
 // Zeroes the exchange words (8 bytes each) of the instance.
 __global__ __launch_bounds__(256) void k_res_zero(u64 *p, int64_t words) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) p[i] = 0ull;
@@ -748,17 +835,19 @@ bool res_plan(int64_t n, int num_cus, int max_rows, ResPlan *pl) {
     ResPlan p{};
     p.ej = (int)((n + 255) / 256);
     p.groups = n <= 512 ? (int)n : 512;
-    const int most = (int)((n + p.groups - 1) / p.groups);   // rows of the largest group
-    p.gpm = max_rows / most;
-    if (p.gpm < 1) return false;
-    p.members = (p.groups + p.gpm - 1) / p.gpm;
-    if (p.members > num_cus) return false;
+    // as many whole groups per member as max_rows hold
     int rows = 0;
-    for (int m = 0; m < p.members; ++m) {
-        const int a = m * p.gpm, b = a + p.gpm < p.groups ? a + p.gpm : p.groups;
-        const int r = (int)((int64_t)b * n / p.groups - (int64_t)a * n / p.groups);
-        rows = r > rows ? r : rows;
+    for (p.gpm = (int)((int64_t)max_rows * p.groups / n); p.gpm >= 1; --p.gpm) {
+        p.members = (p.groups + p.gpm - 1) / p.gpm;
+        rows = 0;
+        for (int m = 0; m < p.members; ++m) {
+            const int a = m * p.gpm, b = a + p.gpm < p.groups ? a + p.gpm : p.groups;
+            const int r = (int)((int64_t)b * n / p.groups - (int64_t)a * n / p.groups);
+            rows = r > rows ? r : rows;
+        }
+        if (rows <= max_rows) break;
     }
+    if (p.gpm < 1 || p.members > num_cus) return false;
     p.rows = rows;
     // the smallest instantiated number of rows per wavefront that holds them
     p.rpw = 0;
@@ -787,6 +876,36 @@ hipError_t launch_res_zero(void *mem, int64_t words, hipStream_t s) {
     const int64_t want = (words + 255) / 256;
     k_res_zero<<<(unsigned)(want < 2048 ? want : 2048), 256, 0, s>>>(static_cast<unsigned long long *>(mem), words);
     return hipGetLastError();
+}
+
+int res_max_rows(int64_t n) {
+    const int ej = (int)((n + 255) / 256);
+    int most = 0;
+#define APX_RES_MOST(e, w) if (ej == e && w > most) most = w;
+    APX_RES_VARIANTS(APX_RES_MOST)
+#undef APX_RES_MOST
+    return most * RW;
+}
+
+bool res_small(int64_t n) { return n <= 256 * kSmallChunks; }
+
+hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
+                                 const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
+                                 int32_t conv_iter, hipStream_t s) {
+    ResArgs a{};
+    a.insts = insts;
+    a.tasks = tasks;
+    a.lane = lane;
+    a.abort = abort;
+    a.lam = a.lam0 = lam;
+    a.max_iter = max_iter;
+    a.conv_iter = conv_iter;
+    const void *f = small ? reinterpret_cast<const void *>(&k_resident_batch<true>)
+                          : reinterpret_cast<const void *>(&k_resident_batch<false>);
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    void *args[] = {&a};
+    return hipLaunchCooperativeKernel(f, dim3(grid), dim3(RT), args, (unsigned)lds, s);
 }
 
 hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,

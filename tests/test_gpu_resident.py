@@ -103,3 +103,37 @@ def test_padding_untouched_and_other_stream():
     R, A = apx.empty_matrix(n), apx.empty_matrix(n)
     idx2, _ = apx.ap_solve(S, R, A, 0.9, 300, 15)
     assert torch.equal(idx, idx2) and torch.equal(r, R) and torch.equal(a, A)
+
+
+@pytest.mark.parametrize("warm", [apx.APX_COLD, apx.APX_WARM_AR])
+@pytest.mark.parametrize("sizes", [[2], [60, 61, 256, 257], [3072, 1025, 1024, 768, 3, 2304], [700] * 24,
+                                   list(range(40, 1024, 41)) * 2])
+def test_batch_equals_single_solves(sizes, warm):
+    """Every instance of a batch as ap_solve gives it, bit for bit: one that
+    fits a single workgroup, both size classes in one call, a batch that fits
+    the chip at once and ones that take turns."""
+    Ss = [_s(n, 2 if n < 300 else 16, 300 + j) for j, n in enumerate(sizes)]
+    start = [(torch.randn(n, n, generator=torch.Generator().manual_seed(n)),
+              -torch.rand(n, n, generator=torch.Generator().manual_seed(n + 1))) for n in sizes]
+
+    def fresh(j):
+        return [apx.to_matrix(m) for m in start[j]]
+
+    RA = [fresh(j) for j in range(len(sizes))]
+    idxs, res = apx.ap_solve_batched(Ss, [r for r, _ in RA], [a for _, a in RA], 0.9, 60, 15, warm=warm)
+    for j, S in enumerate(Ss):
+        R, A = fresh(j)
+        idx, one = apx.ap_solve(S, R, A, 0.9, 60, 15, warm=warm)
+        assert one.iterations == res[j].iterations and one.n_exemplars == res[j].n_exemplars
+        np.testing.assert_array_equal([one.dpsim, one.expref], [res[j].dpsim, res[j].expref])
+        assert torch.equal(idx, idxs[j]) and torch.equal(R, RA[j][0]) and torch.equal(A, RA[j][1])
+
+
+def test_streamed_batch_still_agrees(monkeypatch):
+    sizes = [64, 300, 900]
+    Ss = [_s(n, 16, 500 + n) for n in sizes]
+    idxs, res = apx.ap_solve_batched(Ss, damping=0.9, max_iter=400, conv_iter=15)
+    monkeypatch.setenv("APX_BATCH_WPC", "2")
+    idx2, res2 = apx.ap_solve_batched(Ss, damping=0.9, max_iter=400, conv_iter=15)
+    for a, b, r, q in zip(idxs, idx2, res, res2):
+        assert torch.equal(a, b) and r.iterations == q.iterations
