@@ -311,142 +311,166 @@ __device__ __forceinline__ float gelu_grad(float z) {
            z * 0.39894228040143268f * expf(-0.5f * z * z);
 }
 
-constexpr int FW_T = 256;           // 4 waves
-constexpr int FW_P = 128;           // points per block, 32 per wave
+// The network runs on tiles of 32 points, one workgroup of four wavefronts per
+// tile at a time; wavefront w has units 32 w .. + 31 of both hidden layers.
+// Small tiles because the batches are small: 32 points make 256 workgroups
+// out of 8192 rows, and the chain of dependent steps of a tile (three layers,
+// two of them with a GELU per element, then three products backward), not
+// arithmetic, is what a pass waits for.  The weights are rounded to bf16 into
+// LDS once per workgroup.
+constexpr int TW = 256;             // threads
+constexpr int TP = 32;              // points per tile
 constexpr int LW1 = NF + 4;         // padded row of W1^T in LDS (bf16)
 constexpr int LW2 = NH + 4;         // padded row of W2^T and of the activations
+constexpr int LDZ = NH + 1;         // padded row of a pre-activation gradient
+constexpr int kMaxTileBlocks = 256; // workgroups of the gradient kernel (= partial gradients)
 
-struct FwdShared {
+struct TileShared {
     uint16_t w1t[NH * LW1];         // W1^T [unit][feature]
     uint16_t w2t[NH * LW2];         // W2^T [unit out][unit in]
-    uint16_t h[FW_P * LW2];         // activations [point][unit]
+    uint16_t h1[TP * LW2], h2[TP * LW2];   // activations [point][unit]
     float w3[NH * NO];              // bf16-rounded W3 [unit][output]
     float b1[NH], b2[NH], b3[4];
+    float ypart[TW / 64][64];       // a wavefront's part of the outputs
 };
+
+// Thread -> one output unit and half of the inputs: the loads of a wavefront
+// are consecutive, and four inputs at a time go to the unit's row as one
+// 8-byte write (one 2-byte write per weight took 18 us on conflicting banks).
+__device__ __forceinline__ void tile_weights(TileShared &sh, const float *theta) {
+    const int tid = threadIdx.x, j = tid & (NH - 1), half = tid >> 7;
+    const float *w1 = theta + OFF_W1 + half * (NF / 2) * NH + j, *w2 = theta + OFF_W2 + half * (NH / 2) * NH + j;
+    auto pack = [](float x, float y, float z, float w) {
+        return v4s{(short)bf16_bits(x), (short)bf16_bits(y), (short)bf16_bits(z), (short)bf16_bits(w)};
+    };
+#pragma unroll
+    for (int i = 0; i < NF / 2; i += 4)
+        *reinterpret_cast<v4s *>(sh.w1t + j * LW1 + half * (NF / 2) + i) =
+            pack(w1[i * NH], w1[(i + 1) * NH], w1[(i + 2) * NH], w1[(i + 3) * NH]);
+#pragma unroll
+    for (int i = 0; i < NH / 2; i += 4)
+        *reinterpret_cast<v4s *>(sh.w2t + j * LW2 + half * (NH / 2) + i) =
+            pack(w2[i * NH], w2[(i + 1) * NH], w2[(i + 2) * NH], w2[(i + 3) * NH]);
+    sh.w3[tid] = bf16_val(bf16_bits(theta[OFF_W3 + tid]));
+    if (tid < NH) {
+        sh.b1[tid] = theta[OFF_B1 + tid];
+        sh.b2[tid] = theta[OFF_B2 + tid];
+    }
+    if (tid < NO) sh.b3[tid] = theta[OFF_B3 + tid];
+}
+
+// The features of point lane % 32 of the tile, k = 8 (lane / 32) .. + 7
+// (zeros outside the batch), as bf16.
+__device__ __forceinline__ void tile_features(const float *F, const int64_t *rows, int64_t count, int64_t p0,
+                                              int lane, v4s (&xa)[2]) {
+    const int64_t p = p0 + (lane & 31);
+    const int64_t src = p < count ? (rows ? rows[p] : p) : -1;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float4 f = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (src >= 0) f = *reinterpret_cast<const float4 *>(F + src * NF + (lane >> 5) * 8 + 4 * h);
+        xa[h] = v4s{(short)bf16_bits(f.x), (short)bf16_bits(f.y), (short)bf16_bits(f.z), (short)bf16_bits(f.w)};
+    }
+}
+
+// Bias, GELU and bf16 rounding of this wavefront's 32 x 32 layer output held
+// in MFMA accumulators (lane l holds unit l % 32 and points 8 (v / 4) + 4 (l /
+// 32) + v % 4); GRAD: the GELU's slopes stay in `slope`, in the same places.
+template <bool GRAD>
+__device__ __forceinline__ void tile_epilogue(const v16f &acc, const float *bias, uint16_t *h, int lane, int wave,
+                                              float (&slope)[16]) {
+    const int j = 32 * wave + (lane & 31);
+    const float bj = bias[j];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        const float z = acc[v] + bj;
+        h[r * LW2 + j] = bf16_bits(gelu(z));
+        if (GRAD) slope[v] = gelu_grad(z);
+    }
+}
+
+// Both hidden layers of a tile; ends with a barrier, h1 and h2 complete.
+template <bool GRAD>
+__device__ __forceinline__ void tile_hidden(TileShared &sh, const v4s (&xa)[2], int lane, int wave,
+                                            float (&g1)[16], float (&g2)[16]) {
+    const int li = lane & 31, lk = (lane >> 5) * 8;
+    {
+        const uint16_t *w = sh.w1t + (32 * wave + li) * LW1 + lk;
+        const v16f acc = mfma16(xa[0], xa[1], *reinterpret_cast<const v4s *>(w),
+                                *reinterpret_cast<const v4s *>(w + 4), zero16());
+        tile_epilogue<GRAD>(acc, sh.b1, sh.h1, lane, wave, g1);
+    }
+    __syncthreads();
+    // Layer 2: K = 128 in 8 steps of 16
+    v16f acc = zero16();
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        const uint16_t *hr = sh.h1 + li * LW2 + 16 * ks + lk;
+        const uint16_t *w = sh.w2t + (32 * wave + li) * LW2 + 16 * ks + lk;
+        acc = mfma16(*reinterpret_cast<const v4s *>(hr), *reinterpret_cast<const v4s *>(hr + 4),
+                     *reinterpret_cast<const v4s *>(w), *reinterpret_cast<const v4s *>(w + 4), acc);
+    }
+    tile_epilogue<GRAD>(acc, sh.b2, sh.h2, lane, wave, g2);
+    __syncthreads();
+}
+
+// Output lane / 32 of point lane % 32 (128 -> 2 on the vector units): every
+// wavefront sums its 32 units, the first one adds the four sums.  Ends with a
+// barrier before the sums are read; valid in wavefront 0.
+__device__ __forceinline__ float tile_output(TileShared &sh, int lane, int wave) {
+    const int o = lane >> 5;
+    const uint16_t *hr = sh.h2 + (lane & 31) * LW2 + 32 * wave;
+    const float *w3 = sh.w3 + 32 * wave * NO + o;
+    float y = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 32; j += 4) {
+        const v4s h = *reinterpret_cast<const v4s *>(hr + j);
+        y = fmaf(bf16_val((uint16_t)h.x), w3[j * NO], y);
+        y = fmaf(bf16_val((uint16_t)h.y), w3[(j + 1) * NO], y);
+        y = fmaf(bf16_val((uint16_t)h.z), w3[(j + 2) * NO], y);
+        y = fmaf(bf16_val((uint16_t)h.w), w3[(j + 3) * NO], y);
+    }
+    sh.ypart[wave][lane] = y;
+    __syncthreads();
+    return ((sh.ypart[0][lane] + sh.ypart[1][lane]) + (sh.ypart[2][lane] + sh.ypart[3][lane])) + sh.b3[o];
+}
 
 struct FwdArgs {
     const float *theta;             // FP32 master parameters
     const float *F;                 // features, count x 16
-    const int64_t *rows;            // nullable: point p of the batch is rows[p]
     int64_t count;
     float *Y;                       // count x 2
-    float *Z1, *Z2;                 // nullable stash: pre-activations, count x 128
-    uint16_t *H1, *H2;              // stash: bf16 activations, count x 128
 };
 
-// Bias, GELU and bf16 rounding of one 32 x 128 layer output held in MFMA
-// accumulators; lane l holds column (l % 32) of each 32 x 32 tile and rows
-// 8 (v / 4) + 4 (l / 32) + v % 4 for v < 16.
-template <bool STASH>
-__device__ __forceinline__ void layer_epilogue(const v16f (&acc)[4], const float *bias, uint16_t *hw,
-                                               float *Z, uint16_t *H, int64_t p0, int64_t count,
-                                               int lane) {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int j = 32 * nt + (lane & 31);
-        const float bj = bias[j];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            const float z = acc[nt][v] + bj;
-            const uint16_t hb = bf16_bits(gelu(z));
-            hw[r * LW2 + j] = hb;
-            if (STASH && p0 + r < count) {
-                Z[(p0 + r) * NH + j] = z;
-                H[(p0 + r) * NH + j] = hb;
-            }
-        }
-    }
-}
-
-template <bool STASH>
-__global__ __launch_bounds__(FW_T) void k_mlp_fwd(FwdArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    FwdShared &sh = *reinterpret_cast<FwdShared *>(smem);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int e = tid; e < NF * NH; e += FW_T)
-        sh.w1t[(e % NH) * LW1 + e / NH] = bf16_bits(a.theta[OFF_W1 + e]);
-    for (int e = tid; e < NH * NH; e += FW_T)
-        sh.w2t[(e % NH) * LW2 + e / NH] = bf16_bits(a.theta[OFF_W2 + e]);
-    for (int e = tid; e < NH * NO; e += FW_T) sh.w3[e] = bf16_val(bf16_bits(a.theta[OFF_W3 + e]));
-    for (int e = tid; e < NH; e += FW_T) {
-        sh.b1[e] = a.theta[OFF_B1 + e];
-        sh.b2[e] = a.theta[OFF_B2 + e];
-    }
-    if (tid < NO) sh.b3[tid] = a.theta[OFF_B3 + tid];
-    __syncthreads();
-
-    const int64_t p0 = (int64_t)blockIdx.x * FW_P + wave * 32;
-    const int li = lane & 31, lk = (lane >> 5) * 8;
-    uint16_t *hw = sh.h + (wave * 32) * LW2;
-
-    // Layer 1 (K = 16, one matrix op per 32 units): A operand = bf16
-    // features of point p0 + li, k = lk .. lk + 7.
+// 5000 points: 15 us (47 us with 128 points to a workgroup, 40 of them); the
+// weights' way into LDS and the GELUs take most of it.
+__global__ __launch_bounds__(TW) void k_mlp_fwd(FwdArgs a) {
+    __shared__ __align__(16) TileShared sh;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     v4s xa[2];
-    {
-        const int64_t p = p0 + li;
-        const int64_t src = p < a.count ? (a.rows ? a.rows[p] : p) : -1;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float4 f = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (src >= 0) f = *reinterpret_cast<const float4 *>(a.F + src * NF + lk + 4 * h);
-            xa[h] = v4s{(short)bf16_bits(f.x), (short)bf16_bits(f.y), (short)bf16_bits(f.z),
-                        (short)bf16_bits(f.w)};
+    tile_features(a.F, nullptr, a.count, (int64_t)blockIdx.x * TP, lane, xa);   // in flight with the weights
+    tile_weights(sh, a.theta);
+    __syncthreads();
+    const int64_t tiles = (a.count + TP - 1) / TP;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t p0 = tile * TP;
+        if (tile != blockIdx.x) tile_features(a.F, nullptr, a.count, p0, lane, xa);
+        float g1[16], g2[16];
+        tile_hidden<false>(sh, xa, lane, wave, g1, g2);
+        const float y = tile_output(sh, lane, wave);
+        if (wave == 0) {
+            if (p0 + (lane & 31) < a.count) a.Y[(p0 + (lane & 31)) * NO + (lane >> 5)] = y;
         }
-    }
-    v16f acc[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const uint16_t *w = sh.w1t + (32 * nt + li) * LW1 + lk;
-        acc[nt] = mfma16(xa[0], xa[1], *reinterpret_cast<const v4s *>(w), *reinterpret_cast<const v4s *>(w + 4),
-                         zero16());
-    }
-    layer_epilogue<STASH>(acc, sh.b1, hw, a.Z1, a.H1, p0, a.count, lane);
-    __syncthreads();
-
-    // Layer 2: 32 points x 128 units, K = 128 in 8 steps of 16.
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = zero16();
-#pragma unroll 4
-    for (int ks = 0; ks < 8; ++ks) {
-        const uint16_t *hr = hw + li * LW2 + 16 * ks + lk;
-        const v4s a0 = *reinterpret_cast<const v4s *>(hr), a1 = *reinterpret_cast<const v4s *>(hr + 4);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const uint16_t *w = sh.w2t + (32 * nt + li) * LW2 + 16 * ks + lk;
-            acc[nt] = mfma16(a0, a1, *reinterpret_cast<const v4s *>(w), *reinterpret_cast<const v4s *>(w + 4),
-                             acc[nt]);
-        }
-    }
-    __syncthreads();
-    layer_epilogue<STASH>(acc, sh.b2, hw, a.Z2, a.H2, p0, a.count, lane);
-    __syncthreads();
-
-    // Layer 3 (128 -> 2) on the vector units: lane -> (point li, output lane / 32).
-    {
-        const int o = lane >> 5;
-        float y = 0.0f;
-        const uint16_t *hr = hw + li * LW2;
-        for (int j = 0; j < NH; ++j) y = fmaf(bf16_val(hr[j]), sh.w3[j * NO + o], y);
-        y += sh.b3[o];
-        if (p0 + li < a.count) a.Y[(p0 + li) * NO + o] = y;
+        // (h2 and the sums are written again only after the next tile's first barrier)
     }
 }
-
-// Backward of one block of BW_P points; writes this block's partial gradient.
-constexpr int BW_T = 256;
-constexpr int BW_P = 64;
 
 struct BwdShared {
-    float dz2[BW_P][NH + 1];        // gradient at the second pre-activation
-    uint16_t h1[BW_P][NH + 2];      // bf16 first activations
-    uint16_t w2[NH][NH + 2];        // bf16 W2 [in][out]
-    float x[BW_P][NF + 1];          // bf16-rounded features
-    float dw1[NH][NF + 1];          // second half of the dW1 partial
-    float db1[NH];
-    float dy[BW_P][NO];
-    float w3[NH][NO];
-    double red[BW_T / 64];
+    TileShared t;
+    float dz[TP * LDZ];             // gradient at the second, then the first pre-activation
+    float x[TP * (NF + 1)];         // bf16-rounded features
+    float dy[TP * NO];
 };
 
 struct BwdArgs {
@@ -454,148 +478,175 @@ struct BwdArgs {
     const float *F, *T, *w;         // features (count x 16), targets (count x 2), weights (count)
     const int64_t *rows;            // nullable batch indices into F, T, w
     int64_t count;
-    const float *Y, *Z1, *Z2;       // from the stashing forward pass
-    const uint16_t *H1, *H2;
     float *gpart;                   // [gridDim.x][NPARAM]
     double *lpart;                  // [gridDim.x]
 };
 
-__global__ __launch_bounds__(BW_T) void k_mlp_bwd(BwdArgs a) {
+// Forward and backward of the workgroup's tiles in one kernel (activations
+// and slopes never leave the chip); the products of the backward pass run on
+// the FP32 matrix op (32x32x2: bf16 activations and weights are exact in
+// FP32, gradients stay FP32).  Writes the workgroup's partial gradient.  8192
+// rows: 36 us (forward 52 and backward 149 us while the activations went
+// through memory and the products ran on the vector units).
+__global__ __launch_bounds__(TW) void k_mlp_bwd(BwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     BwdShared &sh = *reinterpret_cast<BwdShared *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t p0 = (int64_t)blockIdx.x * BW_P;
+    const int li = lane & 31, hi = lane >> 5;
     float *g = a.gpart + (int64_t)blockIdx.x * NPARAM;
+    v4s xa[2];
+    tile_features(a.F, a.rows, a.count, (int64_t)blockIdx.x * TP, lane, xa);   // in flight with the weights
+    tile_weights(sh.t, a.theta);
+    __syncthreads();
 
-    for (int e = tid; e < NH * NH; e += BW_T) sh.w2[e / NH][e % NH] = bf16_bits(a.theta[OFF_W2 + e]);
-    for (int e = tid; e < NH * NO; e += BW_T) sh.w3[e / NO][e % NO] = bf16_val(bf16_bits(a.theta[OFF_W3 + e]));
-    for (int e = tid; e < BW_P * NF; e += BW_T) {
-        const int p = e / NF, f = e % NF;
-        float v = 0.0f;
-        if (p0 + p < a.count) {
-            const int64_t src = a.rows ? a.rows[p0 + p] : p0 + p;
-            v = bf16_val(bf16_bits(a.F[src * NF + f]));
-        }
-        sh.x[p][f] = v;
-    }
-    for (int e = tid; e < BW_P * NH; e += BW_T) {
-        const int p = e / NH, j = e % NH;
-        sh.h1[p][j] = p0 + p < a.count ? a.H1[(p0 + p) * NH + j] : (uint16_t)0;
-    }
-    // Loss and its gradient at the outputs: w_p * Huber(y - t), delta 1.
+    v16f dw2[4], dw1 = zero16();    // dW2 rows 32 wave + ., dW1^T-tile: features x units 32 wave + .
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dw2[q] = zero16();
+    float dw3 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f;
     double lsum = 0.0;
-    if (tid < BW_P * NO) {
-        const int p = tid / NO, o = tid % NO;
-        float d = 0.0f;
-        if (p0 + p < a.count) {
-            const int64_t src = a.rows ? a.rows[p0 + p] : p0 + p;
-            const float e = a.Y[(p0 + p) * NO + o] - a.T[src * NO + o];
-            const float wp = a.w[src];
-            d = wp * fminf(1.0f, fmaxf(-1.0f, e));
-            const double ae = fabs((double)e);
-            lsum = (double)wp * (ae <= 1.0 ? 0.5 * (double)e * (double)e : ae - 0.5);
-        }
-        sh.dy[p][o] = d;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
-    if (lane == 0) sh.red[wave] = lsum;
-    __syncthreads();
-    if (tid == 0) {
-        double t = 0.0;
-        for (int w = 0; w < BW_T / 64; ++w) t += sh.red[w];
-        a.lpart[blockIdx.x] = t;
-    }
 
-    // Output layer: dW3[j][o] = sum_p h2[p][j] dy[p][o]; db3.
-    {
-        const int j = tid >> 1, o = tid & 1;
-        float acc = 0.0f;
-        for (int p = 0; p < BW_P && p0 + p < a.count; ++p)
-            acc = fmaf(bf16_val(a.H2[(p0 + p) * NH + j]), sh.dy[p][o], acc);
-        g[OFF_W3 + j * NO + o] = acc;
-        if (tid < NO) {
-            float b = 0.0f;
-            for (int p = 0; p < BW_P; ++p) b += sh.dy[p][tid];
-            g[OFF_B3 + tid] = b;
+    const int64_t tiles = (a.count + TP - 1) / TP;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t p0 = tile * TP;
+        if (tile != blockIdx.x) tile_features(a.F, a.rows, a.count, p0, lane, xa);
+        if (wave == 3) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sh.x[li * (NF + 1) + 8 * hi + 4 * h + e] = bf16_val((uint16_t)xa[h][e]);
         }
-    }
-    // dz2 = (W3 dy) * GELU'(z2)
-    for (int e = tid; e < BW_P * NH; e += BW_T) {
-        const int p = e / NH, j = e % NH;
-        float v = 0.0f;
-        if (p0 + p < a.count) {
-            const float dh = fmaf(sh.w3[j][0], sh.dy[p][0], sh.w3[j][1] * sh.dy[p][1]);
-            v = dh * gelu_grad(a.Z2[(p0 + p) * NH + j]);
-        }
-        sh.dz2[p][j] = v;
-    }
-    __syncthreads();
-
-    // dW2[i][j] = sum_p h1[p][i] dz2[p][j]; thread -> column j, 64 rows i.
-    {
-        const int j = tid & (NH - 1), i0 = (tid >> 7) * 64;
-        float acc[64];
-#pragma unroll
-        for (int q = 0; q < 64; ++q) acc[q] = 0.0f;
-        for (int p = 0; p < BW_P; ++p) {
-            const float dz = sh.dz2[p][j];
-#pragma unroll
-            for (int q = 0; q < 64; ++q) acc[q] = fmaf(bf16_val(sh.h1[p][i0 + q]), dz, acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < 64; ++q) g[OFF_W2 + (i0 + q) * NH + j] = acc[q];
-        if (tid < NH) {
-            float b = 0.0f;
-            for (int p = 0; p < BW_P; ++p) b += sh.dz2[p][tid];
-            g[OFF_B2 + tid] = b;
-        }
-    }
-
-    // dz1 = (W2 dz2) * GELU'(z1); dW1[f][i] = sum_p x[p][f] dz1[p][i]; db1.
-    // Thread -> unit i and one half of the points; halves added in order.
-    {
-        const int i = tid & (NH - 1), half = tid >> 7;
-        float dw[NF];
-#pragma unroll
-        for (int f = 0; f < NF; ++f) dw[f] = 0.0f;
-        float db = 0.0f;
-        for (int p = half * (BW_P / 2); p < (half + 1) * (BW_P / 2); ++p) {
-            if (p0 + p >= a.count) break;
-            float dh = 0.0f;
-            for (int j = 0; j < NH; ++j) dh = fmaf(bf16_val(sh.w2[i][j]), sh.dz2[p][j], dh);
-            const float dz = dh * gelu_grad(a.Z1[(p0 + p) * NH + i]);
-            db += dz;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) dw[f] = fmaf(sh.x[p][f], dz, dw[f]);
-        }
-        if (half == 1) {
-#pragma unroll
-            for (int f = 0; f < NF; ++f) sh.dw1[i][f] = dw[f];
-            sh.db1[i] = db;
+        float g1[16], g2[16];
+        tile_hidden<true>(sh.t, xa, lane, wave, g1, g2);
+        // Loss and its gradient at the outputs: w_p * Huber(y - t), delta 1
+        const float y = tile_output(sh.t, lane, wave);
+        if (wave == 0) {
+            float d = 0.0f;
+            const int64_t p = p0 + li;
+            if (p < a.count) {
+                const int64_t src = a.rows ? a.rows[p] : p;
+                const float e = y - a.T[src * NO + hi];
+                const float wp = a.w[src];
+                d = wp * fminf(1.0f, fmaxf(-1.0f, e));
+                const double ae = fabs((double)e);
+                lsum += (double)wp * (ae <= 1.0 ? 0.5 * (double)e * (double)e : ae - 0.5);
+            }
+            sh.dy[li * NO + hi] = d;
         }
         __syncthreads();
-        if (half == 0) {
+        // dz2 = (W3 dy) * GELU'(z2), in the layout of the layer's output
+        {
+            const int j = 32 * wave + li;
+            const float wa = sh.t.w3[j * NO], wb = sh.t.w3[j * NO + 1];
 #pragma unroll
-            for (int f = 0; f < NF; ++f) g[OFF_W1 + f * NH + i] = dw[f] + sh.dw1[i][f];
-            g[OFF_B1 + i] = db + sh.db1[i];
+            for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
+                sh.dz[r * LDZ + j] = fmaf(wa, sh.dy[r * NO], wb * sh.dy[r * NO + 1]) * g2[v];
+            }
         }
+        // dW3[j][o] = sum_p h2[p][j] dy[p][o]; db3
+        {
+            const int j = tid >> 1, o = tid & 1;
+#pragma unroll 8
+            for (int p = 0; p < TP; ++p) dw3 = fmaf(bf16_val(sh.t.h2[p * LW2 + j]), sh.dy[p * NO + o], dw3);
+            if (tid < NO)
+                for (int p = 0; p < TP; ++p) db3 += sh.dy[p * NO + tid];
+        }
+        __syncthreads();
+        // dW2[i][j] = sum_p h1[p][i] dz2[p][j]; db2
+#pragma unroll 4
+        for (int ks = 0; ks < TP / 2; ++ks) {
+            const int p = 2 * ks + hi;
+            const float av = bf16_val(sh.t.h1[p * LW2 + 32 * wave + li]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                dw2[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * q + li], dw2[q], 0, 0, 0);
+        }
+        if (tid < NH)
+            for (int p = 0; p < TP; ++p) db2 += sh.dz[p * LDZ + tid];
+        // dz1[p][i] = (sum_j dz2[p][j] W2[i][j]) * GELU'(z1): two chains of K
+        v16f s0 = zero16(), s1 = zero16();
+#pragma unroll 8
+        for (int ks = 0; ks < NH / 2; ks += 2) {
+            const int j0 = 2 * ks + hi, j1 = j0 + 2;
+            s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j0],
+                                                      bf16_val(sh.t.w2t[j0 * LW2 + 32 * wave + li]), s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j1],
+                                                      bf16_val(sh.t.w2t[j1 * LW2 + 32 * wave + li]), s1, 0, 0, 0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
+            sh.dz[r * LDZ + 32 * wave + li] = (s0[v] + s1[v]) * g1[v];
+        }
+        __syncthreads();
+        // dW1[f][i] = sum_p x[p][f] dz1[p][i] (16 of the tile's 32 rows); db1
+#pragma unroll 4
+        for (int ks = 0; ks < TP / 2; ++ks) {
+            const int p = 2 * ks + hi;
+            const float av = li < NF ? sh.x[p * (NF + 1) + (li & (NF - 1))] : 0.0f;
+            dw1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * wave + li], dw1, 0, 0, 0);
+        }
+        if (tid < NH)
+            for (int p = 0; p < TP; ++p) db1 += sh.dz[p * LDZ + tid];
+        __syncthreads();
+    }
+
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[OFF_W2 + (32 * wave + r) * NH + 32 * q + li] = dw2[q][v];
+        if (r < NF) g[OFF_W1 + r * NH + 32 * wave + li] = dw1[v];
+    }
+    g[OFF_W3 + tid] = dw3;
+    if (tid < NH) {
+        g[OFF_B1 + tid] = db1;
+        g[OFF_B2 + tid] = db2;
+    }
+    if (tid < NO) g[OFF_B3 + tid] = db3;
+    if (wave == 0) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
+        if (lane == 0) a.lpart[blockIdx.x] = lsum;
     }
 }
 
-// grad[e] = sum over blocks of the partials, in block order (FP64).
-__global__ void k_mlp_reduce(const float *gpart, const double *lpart, int32_t nblk, float *grad,
-                             double *loss) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// grad[e] = sum over workgroups of the partials (FP64): 64 entries x 16
+// slices of the partials per workgroup, slices added in order.  256 partials:
+// 6 us (38 us for 128 with one serial sum per entry).
+__global__ __launch_bounds__(1024) void k_mlp_reduce(const float *gpart, const double *lpart, int32_t nblk,
+                                                     float *grad, double *loss) {
+    __shared__ double part[16][64];
+    const int ex = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + ex;
+    double s = 0.0;
     if (e < NPARAM) {
-        double s = 0.0;
-        for (int b = 0; b < nblk; ++b) s += (double)gpart[(int64_t)b * NPARAM + e];
-        grad[e] = (float)s;
+        int b = sl;
+        for (; b + 7 * 16 < nblk; b += 8 * 16) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = gpart[(int64_t)(b + u * 16) * NPARAM + e];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += (double)v[u];
+        }
+        for (; b < nblk; b += 16) s += (double)gpart[(int64_t)b * NPARAM + e];
     }
-    if (loss && e == 0) {
-        double s = 0.0;
-        for (int b = 0; b < nblk; ++b) s += lpart[b];
-        *loss = s;
+    part[sl][ex] = s;
+    __syncthreads();
+    if (sl == 0 && e < NPARAM) {
+        double tot = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) tot += part[q][ex];
+        grad[e] = (float)tot;
+    }
+    if (loss && blockIdx.x == 0 && sl == 1) {
+        double t = 0.0;
+        for (int b = ex; b < nblk; b += 64) t += lpart[b];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        if (ex == 0) *loss = t;
     }
 }
 
@@ -695,38 +746,26 @@ apx_status run_features(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, Row
     return APX_OK;
 }
 
-apx_status run_forward(apx_ctx *ctx, const FwdArgs &fa, bool stash) {
-    const size_t lds = sizeof(FwdShared);
-    const unsigned grid = (unsigned)((fa.count + FW_P - 1) / FW_P);
-    if (stash) {
-        HIP_TRY(hipFuncSetAttribute((const void *)k_mlp_fwd<true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds), "lds");
-        k_mlp_fwd<true><<<grid, FW_T, lds, ctx->stream>>>(fa);
-    } else {
-        HIP_TRY(hipFuncSetAttribute((const void *)k_mlp_fwd<false>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds), "lds");
-        k_mlp_fwd<false><<<grid, FW_T, lds, ctx->stream>>>(fa);
-    }
+apx_status run_forward(apx_ctx *ctx, const FwdArgs &fa) {
+    const int64_t tiles = (fa.count + TP - 1) / TP;
+    const int64_t most = 2 * (int64_t)ctx->num_cus;      // two workgroups fit a compute unit
+    k_mlp_fwd<<<(unsigned)(tiles < most ? tiles : most), TW, 0, ctx->stream>>>(fa);
     HIP_TRY(hipGetLastError(), "network forward");
     return APX_OK;
 }
 
-int64_t round64(int64_t v) { return (v + 63) & ~int64_t(63); }
 
 struct BwdLayout {
-    size_t o_y, o_z1, o_z2, o_h1, o_h2, o_gp, o_lp, bytes;
+    size_t o_gp, o_lp, bytes;
+    int64_t nblk;
 };
 BwdLayout bwd_layout(int64_t count) {
-    const int64_t nblk = (count + BW_P - 1) / BW_P;
+    const int64_t tiles = (count + TP - 1) / TP;
     WsLayout W;
     BwdLayout o{};
-    o.o_y = W.take(sizeof(float) * NO * (size_t)count);
-    o.o_z1 = W.take(sizeof(float) * NH * (size_t)count);
-    o.o_z2 = W.take(sizeof(float) * NH * (size_t)count);
-    o.o_h1 = W.take(sizeof(uint16_t) * NH * (size_t)count);
-    o.o_h2 = W.take(sizeof(uint16_t) * NH * (size_t)count);
-    o.o_gp = W.take(sizeof(float) * NPARAM * (size_t)nblk);
-    o.o_lp = W.take(sizeof(double) * (size_t)nblk);
+    o.nblk = tiles < kMaxTileBlocks ? tiles : kMaxTileBlocks;
+    o.o_gp = W.take(sizeof(float) * NPARAM * (size_t)o.nblk);
+    o.o_lp = W.take(sizeof(double) * (size_t)o.nblk);
     o.bytes = W.off;
     return o;
 }
@@ -786,7 +825,7 @@ apx_status apx_mlp_forward(apx_ctx *ctx, const float *theta, const float *F, int
     fa.F = F;
     fa.count = count;
     fa.Y = Y;
-    return run_forward(ctx, fa, false);
+    return run_forward(ctx, fa);
 }
 
 apx_status apx_mlp_backward(apx_ctx *ctx, const float *theta, const float *F, const float *T,
@@ -797,23 +836,9 @@ apx_status apx_mlp_backward(apx_ctx *ctx, const float *theta, const float *F, co
         return set_err(ctx, APX_EINVAL, "null or misaligned argument");
     if (count < 1) return set_err(ctx, APX_EINVAL, "count must be >= 1");
     DevGuard g(ctx->device);
-    const int64_t nblk = (count + BW_P - 1) / BW_P;
     const BwdLayout BL = bwd_layout(count);
-    const size_t o_y = BL.o_y, o_z1 = BL.o_z1, o_z2 = BL.o_z2, o_h1 = BL.o_h1, o_h2 = BL.o_h2, o_gp = BL.o_gp,
-                 o_lp = BL.o_lp;
     APX_TRY(ws_reserve(ctx, ctx->ws_base + BL.bytes));
     char *b = static_cast<char *>(ctx->ws) + ctx->ws_base;
-    FwdArgs fa{};
-    fa.theta = theta;
-    fa.F = F;
-    fa.rows = rows;
-    fa.count = count;
-    fa.Y = reinterpret_cast<float *>(b + o_y);
-    fa.Z1 = reinterpret_cast<float *>(b + o_z1);
-    fa.Z2 = reinterpret_cast<float *>(b + o_z2);
-    fa.H1 = reinterpret_cast<uint16_t *>(b + o_h1);
-    fa.H2 = reinterpret_cast<uint16_t *>(b + o_h2);
-    APX_TRY(run_forward(ctx, fa, true));
     BwdArgs ba{};
     ba.theta = theta;
     ba.F = F;
@@ -821,19 +846,14 @@ apx_status apx_mlp_backward(apx_ctx *ctx, const float *theta, const float *F, co
     ba.w = w;
     ba.rows = rows;
     ba.count = count;
-    ba.Y = fa.Y;
-    ba.Z1 = fa.Z1;
-    ba.Z2 = fa.Z2;
-    ba.H1 = fa.H1;
-    ba.H2 = fa.H2;
-    ba.gpart = reinterpret_cast<float *>(b + o_gp);
-    ba.lpart = reinterpret_cast<double *>(b + o_lp);
+    ba.gpart = reinterpret_cast<float *>(b + BL.o_gp);
+    ba.lpart = reinterpret_cast<double *>(b + BL.o_lp);
     const size_t lds = sizeof(BwdShared);
     HIP_TRY(hipFuncSetAttribute((const void *)k_mlp_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds), "lds");
-    k_mlp_bwd<<<(unsigned)nblk, BW_T, lds, ctx->stream>>>(ba);
+    k_mlp_bwd<<<(unsigned)BL.nblk, TW, lds, ctx->stream>>>(ba);
     HIP_TRY(hipGetLastError(), "network backward");
-    k_mlp_reduce<<<(NPARAM + 255) / 256, 256, 0, ctx->stream>>>(ba.gpart, ba.lpart, (int32_t)nblk, grad, loss);
+    k_mlp_reduce<<<(NPARAM + 63) / 64, 1024, 0, ctx->stream>>>(ba.gpart, ba.lpart, (int32_t)BL.nblk, grad, loss);
     HIP_TRY(hipGetLastError(), "gradient reduce");
     return APX_OK;
 }
@@ -902,7 +922,7 @@ apx_status ap_warmstart(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, con
     fa.F = F;
     fa.count = n;
     fa.Y = Yp;
-    APX_TRY(run_forward(ctx, fa, false));
+    APX_TRY(run_forward(ctx, fa));
     k_warm_a0<<<grid_rows(n, ctx->num_cus * 4), 256, 0, ctx->stream>>>(Yp, sg, (int32_t)n, A, ld);
     HIP_TRY(hipGetLastError(), "A_0");
     // R_0 = one undamped responsibility step (Eq. (2)) from A_0.
