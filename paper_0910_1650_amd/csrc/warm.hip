@@ -171,68 +171,255 @@ constexpr int Q50 = 9;  // index of the median in RowStats::v
 __constant__ int kDesc[6] = {0, 1, 3, 7, 15, 31};
 __constant__ int kQuant[5] = {1, 10, 25, 50, 75};
 
-__global__ __launch_bounds__(SEL_T) void k_row_stats(const float *S, int64_t ld, int32_t n,
-                                                     RowStats *out) {
-    __shared__ SelShared sm;
-    __shared__ double wsum[SEL_T / 64];
-    __shared__ int32_t wcnt[SEL_T / 64][2];
+// Ascending rank of the q-th order statistic among the row's m values.
+__device__ __forceinline__ int32_t stat_rank(int q, int64_t m) {
+    if (q >= 6) return (int32_t)(((int64_t)kQuant[q - 6] * (m - 1)) / 100);
+    const int64_t j = kDesc[q];
+    return (int32_t)(m - 1 - (j < m - 1 ? j : m - 1));
+}
+
+// From the keys of the order statistics: the sum of the 32 largest and the
+// elements above the diagonal; writes the row's statistics.
+template <int T, class Each>
+__device__ __forceinline__ void row_tail(Each each, const uint32_t *keys, float dg, int64_t m, double *wsum,
+                                         int32_t *wcnt, RowStats *out) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t key32 = keys[5];
+    double s = 0.0;
+    int32_t gt = 0, above = 0;
+    each([&](float x) {
+        if (fkey(x) > key32) {
+            s += (double)x;
+            ++gt;
+        }
+        above += (x > dg) ? 1 : 0;
+    });
+    // (the counts as one word: at most 65536 and 31)
+    int32_t both = above << 6 | gt;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        s += __shfl_down(s, off, 64);
+        both += __shfl_down(both, off, 64);
+    }
+    if (lane == 0) {
+        wsum[wave] = s;
+        wcnt[wave] = both;
+    }
+    __syncthreads();
+    if (tid < NTGT) out->v[tid] = keyf(keys[tid]);
+    if (wave == 1) {
+        double tot = lane < T / 64 ? wsum[lane] : 0.0;
+        both = lane < T / 64 ? wcnt[lane] : 0;
+#pragma unroll
+        for (int off = T / 128; off > 0; off >>= 1) {
+            tot += __shfl_down(tot, off, 64);
+            both += __shfl_down(both, off, 64);
+        }
+        if (lane > 0) return;
+        const int32_t a = both >> 6, g = both & 63;
+        const int32_t cnt = m < TOP ? (int32_t)m : TOP;
+        out->diag = dg;
+        out->above = a;
+        out->pad = 0;
+        out->top_sum = tot + (double)(cnt - g) * (double)keyf(key32);
+    }
+}
+
+// Order statistics of one row, all eleven at once.  The row is cut into
+// kBins intervals of equal width between its least and largest value; the
+// cut is a monotone function of the value, so the counts of the intervals
+// tell which one holds each rank.  The few keys of those intervals are
+// collected and ranked by counting.  Against the digits of a radix select
+// (four passes, whose first digits are the exponent and put most of a row on
+// a few LDS counters) a row takes two passes over registers: 5000 rows of
+// 5000 85 us, 514 before.  A row whose values crowd (many ties: more than
+// kCand keys in the eleven intervals) is left to the radix select below.
+constexpr int ST_T = 512;
+constexpr int kBins = 2048, kCand = 1024;
+static_assert(kBins == 4 * ST_T, "four intervals per thread");
+
+struct BinShared {
+    uint32_t hist[kBins];
+    uint8_t mark[kBins];       // 1 + list of an interval that holds a rank
+    uint32_t cand[kCand];      // keys of those intervals, list by list
+    uint32_t wtot[ST_T / 64];
+    int32_t bin[NTGT], rank[NTGT], cnt[NTGT];   // a rank's interval, its rank in it, the interval's keys
+    int32_t off[NTGT];         // first key of a rank's list
+    int32_t cursor[NTGT];      // by list
+    int32_t total;
+    float lo[ST_T / 16], hi[ST_T / 16];
+    uint32_t key[NTGT];
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+// E > 0: the row (n <= E * ST_T) is held in registers; 0: read again.
+template <int E>
+__global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *S, int64_t ld, int32_t n, RowStats *out) {
+    __shared__ BinShared bs;
+    __shared__ double wsum[ST_T / 64];
+    __shared__ int32_t wcnt[ST_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = ST_T / 64;
     const int64_t m = n - 1;
+    const int32_t want = lane < NTGT ? stat_rank(lane, m) : 0;   // the ranks, lane by lane
     for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
         const float *row = S + k * ld;
-        if (tid < NTGT) {
-            int64_t r;
-            if (tid < 6) {
-                const int64_t j = kDesc[tid];
-                r = m - 1 - (j < m - 1 ? j : m - 1);
-            } else {
-                r = ((int64_t)kQuant[tid - 6] * (m - 1)) / 100;
+        float v[E > 0 ? E : 1];
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int j = tid + e * ST_T;
+                v[e] = j < n ? row[j] : 0.0f;
             }
-            sm.rank[tid] = (int32_t)r;
         }
-        radix_select(sm, m, NTGT, [&](int64_t j) { return fkey(row[j < k ? j : j + 1]); });
-        // Elements above the 32nd largest, and elements above the diagonal.
-        const uint32_t key32 = sm.pref[5];
-        const float dg = row[k];
-        double s = 0.0;
-        int32_t gt = 0, above = 0;
-        for (int64_t j = tid; j < m; j += blockDim.x) {
-            const float v = row[j < k ? j : j + 1];
-            if (fkey(v) > key32) {
-                s += (double)v;
-                ++gt;
+        auto each = [&](auto f) {
+            if constexpr (E > 0) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int j = tid + e * ST_T;
+                    if (j < n && j != (int)k) f(v[e]);
+                }
+            } else {
+                for (int64_t j = tid; j < n; j += ST_T)
+                    if (j != k) f(row[j]);
             }
-            above += (v > dg) ? 1 : 0;
+        };
+        float lo = INFINITY, hi = -INFINITY;
+        each([&](float x) {
+            lo = fminf(lo, x);
+            hi = fmaxf(hi, x);
+        });
+        // over each 16 lanes (quad swaps, half-row and row mirrors)
+        lo = fminf(lo, dpp_mov<0xB1>(lo)), hi = fmaxf(hi, dpp_mov<0xB1>(hi));
+        lo = fminf(lo, dpp_mov<0x4E>(lo)), hi = fmaxf(hi, dpp_mov<0x4E>(hi));
+        lo = fminf(lo, dpp_mov<0x141>(lo)), hi = fmaxf(hi, dpp_mov<0x141>(hi));
+        lo = fminf(lo, dpp_mov<0x140>(lo)), hi = fmaxf(hi, dpp_mov<0x140>(hi));
+        if ((lane & 15) == 0) {
+            bs.lo[tid >> 4] = lo;
+            bs.hi[tid >> 4] = hi;
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            s += __shfl_down(s, off, 64);
-            gt += __shfl_down(gt, off, 64);
-            above += __shfl_down(above, off, 64);
+        for (int q = 0; q < 4; ++q) bs.hist[tid + q * ST_T] = 0u;
+        reinterpret_cast<uint32_t *>(bs.mark)[tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < ST_T / 64; ++w) {
+            const float4 a = *reinterpret_cast<const float4 *>(&bs.lo[4 * w]);
+            const float4 b = *reinterpret_cast<const float4 *>(&bs.hi[4 * w]);
+            lo = fminf(fminf(fminf(lo, a.x), fminf(a.y, a.z)), a.w);
+            hi = fmaxf(fmaxf(fmaxf(hi, b.x), fmaxf(b.y, b.z)), b.w);
         }
-        if (lane == 0) {
-            wsum[wave] = s;
-            wcnt[wave][0] = gt;
-            wcnt[wave][1] = above;
+        const float inv = (float)(kBins - 1) / (hi - lo);
+        auto bin_of = [&](float x) -> int {
+            const int b = (int)((x - lo) * inv);
+            return b < 0 ? 0 : b > kBins - 1 ? kBins - 1 : b;
+        };
+        each([&](float x) { atomicAdd(&bs.hist[bin_of(x)], 1u); });
+        __syncthreads();
+        // the intervals that hold the ranks
+        {
+            const uint4 h = *reinterpret_cast<const uint4 *>(&bs.hist[4 * tid]);
+            const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
+            uint32_t inc = tot;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t o = __shfl_up(inc, off, 64);
+                if (lane >= off) inc += o;
+            }
+            if (lane == 63) bs.wtot[wave] = inc;
+            __syncthreads();
+            uint32_t before = inc - tot;
+            for (int w = 0; w < wave; ++w) before += bs.wtot[w];
+#pragma unroll
+            for (int q = 0; q < NTGT; ++q) {
+                const uint32_t r = (uint32_t)__builtin_amdgcn_readlane(want, q);
+                if (r >= before && r < before + tot) {
+                    uint32_t acc = before;
+                    int d = 0;
+                    while (d < 3 && r >= acc + c[d]) acc += c[d++];
+                    bs.bin[q] = 4 * tid + d;
+                    bs.rank[q] = (int32_t)(r - acc);
+                    bs.cnt[q] = (int32_t)c[d];
+                }
+            }
         }
         __syncthreads();
-        if (tid == 0) {
-            double tot = 0.0;
-            int32_t g = 0, a = 0;
-            for (int w = 0; w < SEL_T / 64; ++w) {
-                tot += wsum[w];
-                g += wcnt[w][0];
-                a += wcnt[w][1];
+        // one list per interval: lane q has rank q; equal intervals share the
+        // first one's list
+        if (wave == 0) {
+            const int b = lane < NTGT ? bs.bin[lane] : -1 - lane;
+            const int c = lane < NTGT ? bs.cnt[lane] : 0;
+            int first = lane;
+#pragma unroll
+            for (int q = NTGT - 1; q >= 0; --q)
+                if (__builtin_amdgcn_readlane(b, q) == b && q < first) first = q;
+            const bool own = lane < NTGT && first == lane;
+            int at = 0, total = 0;
+#pragma unroll
+            for (int q = 0; q < NTGT; ++q) {
+                const int cq = __builtin_amdgcn_readlane(own ? c : 0, q);
+                if (q < first) at += cq;
+                total += cq;
             }
-            const int32_t cnt = m < TOP ? (int32_t)m : TOP;
-            RowStats r;
-            for (int t = 0; t < NTGT; ++t) r.v[t] = keyf(sm.pref[t]);
-            r.diag = dg;
-            r.above = a;
-            r.pad = 0;
-            r.top_sum = tot + (double)(cnt - g) * (double)keyf(key32);
-            out[k] = r;
+            if (lane < NTGT) bs.off[lane] = at;
+            if (own) {
+                bs.mark[b] = (uint8_t)(1 + lane);
+                bs.cursor[lane] = at;
+            }
+            if (lane == 0) bs.total = total;
         }
+        __syncthreads();
+        const bool crowded = bs.total > kCand;
+        if (!crowded) {
+            each([&](float x) {
+                const int q = bs.mark[bin_of(x)];
+                if (q) bs.cand[atomicAdd(&bs.cursor[q - 1], 1)] = fkey(x);
+            });
+            __syncthreads();
+            for (int q = wave; q < NTGT; q += NW) {
+                const uint32_t *l = bs.cand + bs.off[q];
+                const int c = bs.cnt[q], r = bs.rank[q];
+                for (int e = lane; e < c; e += 64) {
+                    const uint32_t x = l[e];
+                    int less = 0, same = 0;
+#pragma unroll 4
+                    for (int i = 0; i < c; ++i) {
+                        less += l[i] < x;
+                        same += l[i] == x;
+                    }
+                    if (r >= less && r < less + same) bs.key[q] = x;   // (equal keys write the same)
+                }
+            }
+        }
+        __syncthreads();
+        if (crowded) {
+            if (tid == 0) out[k].pad = 1;      // left to k_row_stats_radix
+            continue;
+        }
+        row_tail<ST_T>(each, bs.key, row[k], m, wsum, wcnt, out + k);
+        __syncthreads();
+    }
+}
+
+// The rows that k_row_stats left, by radix select.
+__global__ __launch_bounds__(SEL_T) void k_row_stats_radix(const float *S, int64_t ld, int32_t n, RowStats *out) {
+    __shared__ SelShared sm;
+    __shared__ double wsum[SEL_T / 64];
+    __shared__ int32_t wcnt[SEL_T / 64];
+    const int tid = threadIdx.x;
+    const int64_t m = n - 1;
+    for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
+        if (out[k].pad == 0) continue;
+        const float *row = S + k * ld;
+        if (tid < NTGT) sm.rank[tid] = stat_rank(tid, m);
+        radix_select(sm, m, NTGT, [&](int64_t j) { return fkey(row[j < k ? j : j + 1]); });
+        row_tail<SEL_T>([&](auto f) {
+            for (int64_t j = tid; j < n; j += SEL_T)
+                if (j != k) f(row[j]);
+        }, sm.pref, row[k], m, wsum, wcnt, out + k);
         __syncthreads();
     }
 }
@@ -736,7 +923,13 @@ unsigned grid_rows(int64_t n, int num_cus) {
 apx_status run_features(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, RowStats *stats,
                         float *F, float *sigma) {
     hipStream_t s = ctx->stream;
-    k_row_stats<<<grid_rows(n, ctx->num_cus), SEL_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    const unsigned rows = grid_rows(n, ctx->num_cus * 4);     // four workgroups fit a compute unit
+    if (n <= 2 * ST_T) k_row_stats<2><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    else if (n <= 4 * ST_T) k_row_stats<4><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    else if (n <= 8 * ST_T) k_row_stats<8><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    else if (n <= 16 * ST_T) k_row_stats<16><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    else k_row_stats<0><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    k_row_stats_radix<<<grid_rows(n, ctx->num_cus), SEL_T, 0, s>>>(S, ld, (int32_t)n, stats);
     HIP_TRY(hipGetLastError(), "row statistics");
     k_sigma<<<1, SEL_T, 0, s>>>(stats, (int32_t)n, sigma);
     HIP_TRY(hipGetLastError(), "sigma");

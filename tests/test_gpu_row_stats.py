@@ -1,0 +1,34 @@
+"""Row statistics of the warm-start features at the edges of their kernel: the
+rows held in registers (up to 2, 4, 8, 16 elements per thread) and reread
+above, rows whose values crowd into few intervals (ties, one far outlier, all
+equal, both zeros) and so take the radix select, next to rows that do not.
+Order statistics are exact, so every feature equals the oracle's bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_0910_1650_amd as apx
+import synth
+from oracle import warm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [2, 3, 33, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
+def test_features_equal_oracle(n):
+    pts = synth.gaussian_mixture(n=n, d=8, k=5, seed=n)
+    S, _ = apx.ap_similarity(torch.from_numpy(pts.X).cuda(), noise_seed=1)
+    g = torch.Generator().manual_seed(n)
+    if n > 100:
+        S[1] = -3.0                                            # all equal
+        S[2] = torch.randint(-4, 0, (n,), generator=g).float().cuda()   # four values
+        S[3, 17] = -1.0e30                                     # one outlier: the rest in one interval
+        S[4] = torch.where(torch.rand(n, generator=g) < 0.5, 0.0, -0.0).cuda()
+        S[5] = -torch.arange(n).float().cuda()                 # evenly spread
+    F, sig = apx.apx_features(S)
+    rows = np.unique(np.concatenate([np.arange(min(n, 8)), np.random.default_rng(n).integers(0, n, 12)]))
+    ref, _ = warm.features(S.cpu().numpy().astype(np.float64), rows=rows, sigma=float(sig))
+    np.testing.assert_array_equal(F.cpu().numpy()[rows], ref.astype(np.float32))
+    med = np.sort(np.partition(S.cpu().numpy()[~np.eye(n, dtype=bool)].reshape(n, n - 1), (n - 2) // 2, axis=1)[:, (n - 2) // 2])
+    assert float(sig) == abs(med[(n - 1) // 2])
