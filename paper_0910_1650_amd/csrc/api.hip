@@ -489,24 +489,11 @@ size_t solve_ws_bytes(int64_t n, int64_t ld, int num_cus) {
     return iter_layout(n, ld, true, pl.grid).bytes;
 }
 
-size_t resp_step_ws_bytes(int64_t n, int64_t ld, int num_cus) {
+size_t iterate_ws_bytes(int64_t n, int64_t ld, int num_cus) {
     const PassPlan pl = plan_pass(n, num_cus);
     return iter_layout(n, ld, false, pl.grid).bytes;
 }
 
-apx_status resp_step(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *R, float *A) {
-    PassPlan pl{};
-    APX_TRY(ctx_plan(ctx, n, &pl, nullptr));
-    IterWs w{};
-    APX_TRY(iter_ws(ctx, n, ld, false, pl, w));
-    hipStream_t s = ctx->stream;
-    // With damping 0 and R = 0 the responsibility pass computes
-    // 0 * 0 + 1 * s(i,k) - 1 * max(...) exactly: the plain update of Eq. (2).
-    HIP_TRY(launch_fill_f32_rows(R, n, n, ld, 0.0f, s), "R = 0");
-    PassArgs pa = pass_args(S, R, R, A, n, ld, 0.0f, w, nullptr, nullptr, nullptr);
-    HIP_TRY(launch_row_pass(pl, PASS_R_ONLY, pa, s), "responsibility step");
-    return APX_OK;
-}
 }  // namespace apx
 
 extern "C" {
@@ -604,7 +591,7 @@ size_t apx_workspace_size(const apx_ctx *ctx, int32_t op, int64_t n, int64_t ld,
     case APX_OP_SIMILARITY:
         return n >= 2 ? similarity_ws_bytes(n) : 0;
     case APX_OP_ITERATE:
-        return (n >= 2 && ld >= n) ? resp_step_ws_bytes(n, ld, cus) : 0;
+        return (n >= 2 && ld >= n) ? iterate_ws_bytes(n, ld, cus) : 0;
     case APX_OP_SOLVE:
         return (n >= 1 && ld >= n) ? solve_ws_bytes(n, ld, cus) : 0;
     case APX_OP_SOLVE_BATCHED: {
@@ -625,7 +612,7 @@ size_t apx_workspace_size(const apx_ctx *ctx, int32_t op, int64_t n, int64_t ld,
     case APX_OP_MLP_BACKWARD:
         return count >= 1 ? mlp_backward_ws_bytes(count) : 0;
     case APX_OP_WARMSTART:
-        return (n >= 2 && ld >= n) ? warmstart_ws_bytes(n, ld, cus) : 0;
+        return (n >= 2 && ld >= n) ? warmstart_ws_bytes(n) : 0;
     case APX_OP_LAP_FULL:
         return (n >= 2 && d >= 1 && count >= 2 && count <= n && ld >= 2) ? lap_full_ws_bytes(n, d, count, ld, cus)
                                                                           : 0;

@@ -417,7 +417,7 @@ size_t lap_ws_bytes(int64_t n, int64_t d, int64_t L, int num_cus);
 size_t lap_full_ws_bytes(int64_t n, int64_t d, int64_t L, int64_t m0, int num_cus);
 size_t features_ws_bytes(int64_t n);
 size_t mlp_backward_ws_bytes(int64_t count);
-size_t warmstart_ws_bytes(int64_t n, int64_t ld, int num_cus);
+size_t warmstart_ws_bytes(int64_t n);
 // APX_EINVAL (with a message) if any entry of the n x n matrix M is not
 // finite; synchronises the context stream.
 apx_status check_finite(apx_ctx *ctx, const float *M, int64_t n, int64_t ld, const char *name);
@@ -427,11 +427,7 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
                          const apx_params *params, apx_result *res);
 // Single-instance solve on the workspace slice starting at ctx->ws_base.
 size_t solve_ws_bytes(int64_t n, int64_t ld, int num_cus);
-// R := the undamped responsibility update of Eq. (2) computed from (S, A),
-// i.e. r(i,k) = s(i,k) - max_{k' != k} (a(i,k') + s(i,k')); R's previous
-// contents are not used.  Workspace slice at ctx->ws_base.
-apx_status resp_step(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *R, float *A);
-size_t resp_step_ws_bytes(int64_t n, int64_t ld, int num_cus);
+size_t iterate_ws_bytes(int64_t n, int64_t ld, int num_cus);
 apx_status set_err(apx_ctx *ctx, apx_status st, const char *fmt, ...);
 // Row-pass plan for n on this context: the default plan with the tuned
 // workgroup size and variant applied (tuning first if enabled and unseen);

@@ -893,6 +893,115 @@ __global__ void k_warm_a0(const float *Y, const float *sigma, int32_t n, float *
     }
 }
 
+// A_0 and R_0 of a row in one pass over S: A_0 as k_warm_a0 writes it and
+// r(i,k) = s(i,k) - max_{k' != k} (a_0(i,k') + s(i,k')) (the undamped Eq. (2)).
+// A workgroup takes whole rows; thread l of T holds the float4 chunks at
+// columns 4 (l + j T) of the row and of A_0's column values, which stay in
+// registers over all its rows.  The largest a + s takes the second largest
+// value; under a tie the two are equal, so comparing values names it.  Reads
+// S, writes A and R: 12 bytes per element (5000 points 54 us, 5.5 TB/s; A_0, R = 0 and
+// the general responsibility pass took 149 us and 24 bytes).
+template <int T, int J>
+__global__ __launch_bounds__(T) void k_warm_start(const float *S, const float *Y, const float *sigma, int32_t n,
+                                                  int64_t ld, float *A, float *R) {
+#pragma clang fp contract(off)
+    __shared__ float sh[2][T / 64][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float sg = *sigma;
+    float col[J][4];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 4 * (tid + j * T) + e;
+            col[j][e] = k < n ? a0_value(Y, sg, -1, k) : 0.0f;
+        }
+    int slot = 0;
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x, slot ^= 1) {
+        const float *srow = S + i * ld;
+        const float ad = a0_value(Y, sg, i, i);
+        constexpr bool HOLD = J <= 8;        // else the row is read again after the reduction
+        float x[HOLD ? J : 1][4];
+        auto load = [&](int j, float (&o)[4]) {
+            const int c = 4 * (tid + j * T);
+            float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (c < n) g = *reinterpret_cast<const float4 *>(srow + c);
+            o[0] = g.x;
+            o[1] = g.y;
+            o[2] = g.z;
+            o[3] = g.w;
+        };
+        if constexpr (HOLD)
+#pragma unroll
+            for (int j = 0; j < J; ++j) load(j, x[j]);
+        float v1 = -INFINITY, v2 = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            float (&xs)[4] = x[HOLD ? j : 0];
+            if constexpr (!HOLD) load(j, xs);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * (tid + j * T) + e;
+                const float v = k < n ? (k == (int)i ? ad : col[j][e]) + xs[e] : -INFINITY;
+                v2 = fmaxf(v2, fminf(v1, v));
+                v1 = fmaxf(v1, v);
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const float o1 = __shfl_xor(v1, off, 64), o2 = __shfl_xor(v2, off, 64);
+            v2 = fmaxf(fmaxf(v2, o2), fminf(v1, o1));
+            v1 = fmaxf(v1, o1);
+        }
+        if (lane == 0) {
+            sh[slot][wave][0] = v1;
+            sh[slot][wave][1] = v2;
+        }
+        __syncthreads();
+        v1 = v2 = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < T / 64; ++w) {
+            const float o1 = sh[slot][w][0], o2 = sh[slot][w][1];
+            v2 = fmaxf(fmaxf(v2, o2), fminf(v1, o1));
+            v1 = fmaxf(v1, o1);
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int c = 4 * (tid + j * T);
+            if (c >= n) continue;
+            float (&xs)[4] = x[HOLD ? j : 0];
+            if constexpr (!HOLD) load(j, xs);
+            float ao[4], ro[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                asm volatile("" : "+v"(xs[e]));      // a + s is formed again, not held
+                ao[e] = c + e == (int)i ? ad : col[j][e];
+                ro[e] = xs[e] - (ao[e] + xs[e] == v1 ? v2 : v1);
+            }
+            float *ar = A + i * ld + c, *rr = R + i * ld + c;
+            if (c + 3 < n) {
+                *reinterpret_cast<float4 *>(ar) = make_float4(ao[0], ao[1], ao[2], ao[3]);
+                *reinterpret_cast<float4 *>(rr) = make_float4(ro[0], ro[1], ro[2], ro[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (c + e < n) {
+                        ar[e] = ao[e];
+                        rr[e] = ro[e];
+                    }
+            }
+        }
+    }
+}
+
+template <int T, int J>
+void launch_warm_start(const float *S, const float *Y, const float *sigma, int64_t n, int64_t ld, float *A, float *R,
+                       int num_cus, hipStream_t s) {
+    // as many workgroups as are resident, so that a column vector is read once
+    const int64_t g = (int64_t)num_cus * (T == 256 ? 8 : 2);
+    k_warm_start<T, J><<<(unsigned)(n < g ? n : g), T, 0, s>>>(S, Y, sigma, (int32_t)n, ld, A, R);
+}
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 struct DevGuard {
@@ -986,9 +1095,7 @@ size_t features_ws_bytes(int64_t n) {
     return W.off;
 }
 size_t mlp_backward_ws_bytes(int64_t count) { return bwd_layout(count).bytes; }
-size_t warmstart_ws_bytes(int64_t n, int64_t ld, int num_cus) {
-    return warm_layout(n).head + resp_step_ws_bytes(n, ld, num_cus);
-}
+size_t warmstart_ws_bytes(int64_t n) { return warm_layout(n).head; }
 }  // namespace apx
 
 extern "C" {
@@ -1101,9 +1208,9 @@ apx_status ap_warmstart(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, con
     if (!theta) return set_err(ctx, APX_EINVAL, "theta is null");
     DevGuard g(ctx->device);
     const WarmLayout WL = warm_layout(n);
-    const size_t o_st = WL.o_st, o_f = WL.o_f, o_y = WL.o_y, o_s = WL.o_s, head = WL.head;
+    const size_t o_st = WL.o_st, o_f = WL.o_f, o_y = WL.o_y, o_s = WL.o_s;
     const size_t base = ctx->ws_base;
-    APX_TRY(ws_reserve(ctx, base + head + resp_step_ws_bytes(n, ld, ctx->num_cus)));
+    APX_TRY(ws_reserve(ctx, base + WL.head));
     char *b = static_cast<char *>(ctx->ws) + base;
     RowStats *stats = reinterpret_cast<RowStats *>(b + o_st);
     float *F = reinterpret_cast<float *>(b + o_f);
@@ -1116,13 +1223,19 @@ apx_status ap_warmstart(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, con
     fa.count = n;
     fa.Y = Yp;
     APX_TRY(run_forward(ctx, fa));
-    k_warm_a0<<<grid_rows(n, ctx->num_cus * 4), 256, 0, ctx->stream>>>(Yp, sg, (int32_t)n, A, ld);
-    HIP_TRY(hipGetLastError(), "A_0");
-    // R_0 = one undamped responsibility step (Eq. (2)) from A_0.
-    ctx->ws_base = base + head;
-    const apx_status st = resp_step(ctx, S, n, ld, R, A);
-    ctx->ws_base = base;
-    return st;
+    // A_0, and R_0 = one undamped responsibility step (Eq. (2)) from it
+    hipStream_t s = ctx->stream;
+    const int64_t q = (n + 3) / 4;
+    const int cus = ctx->num_cus;
+    if (q <= 256) launch_warm_start<256, 1>(S, Yp, sg, n, ld, A, R, cus, s);
+    else if (q <= 512) launch_warm_start<256, 2>(S, Yp, sg, n, ld, A, R, cus, s);
+    else if (q <= 1024) launch_warm_start<256, 4>(S, Yp, sg, n, ld, A, R, cus, s);
+    else if (q <= 2048) launch_warm_start<1024, 2>(S, Yp, sg, n, ld, A, R, cus, s);
+    else if (q <= 4096) launch_warm_start<1024, 4>(S, Yp, sg, n, ld, A, R, cus, s);
+    else if (q <= 8192) launch_warm_start<1024, 8>(S, Yp, sg, n, ld, A, R, cus, s);
+    else launch_warm_start<1024, 16>(S, Yp, sg, n, ld, A, R, cus, s);
+    HIP_TRY(hipGetLastError(), "starting messages");
+    return APX_OK;
 }
 
 }  // extern "C"
