@@ -6,9 +6,14 @@
 // accumulate).  Only tiles on or above the block diagonal are computed; each
 // result is written at (i,k) and mirrored to (k,i) from the accumulators,
 // so S is exactly symmetric.  The preference is the median of the n(n-1) off-diagonal
-// entries, found exactly by a three-pass radix select over the upper
-// triangle (which holds every off-diagonal value twice by symmetry).
+// entries, found exactly without reading S again: a sample of pairs gives a
+// narrow window of values that holds the median, the tiles count the upper
+// entries below it and set aside those inside it, and the few set aside are
+// ranked.  (The upper triangle holds every off-diagonal value twice by
+// symmetry.)  Should the window miss, or too many values fall into it, a
+// three-pass radix select over the stored upper triangle finds it instead.
 #include <cmath>
+#include <type_traits>
 
 #include "apx_internal.h"
 
@@ -37,13 +42,76 @@ __device__ __forceinline__ float keyf(uint32_t k) {
     return __uint_as_float(b);
 }
 
-__global__ void k_sqnorm(const float *X, int64_t n, int64_t d, int64_t ldx, float *nrm) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float *x = X + i * ldx;
+// Squared norms, summed in column order; bad (nullable): set where X holds a
+// NaN or an infinity.  64 rows per workgroup go through LDS 64 columns at a
+// time, so that the loads are coalesced (5003 x 62: 7.5 us against 14 with one
+// thread reading along a row).
+__global__ __launch_bounds__(256) void k_sqnorm(const float *X, int64_t n, int64_t d, int64_t ldx, float *nrm,
+                                                int32_t *bad) {
+    __shared__ float sh[64][65];
+    const int tid = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
     float acc = 0.0f;
-    for (int64_t j = 0; j < d; ++j) acc = fmaf(x[j], x[j], acc);
-    nrm[i] = acc;
+    uint32_t nonfinite = 0u;
+    for (int64_t c0 = 0; c0 < d; c0 += 64) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int e = tid + 256 * u, r = e >> 6, c = e & 63;
+            const float x = r0 + r < n && c0 + c < d ? X[(r0 + r) * ldx + c0 + c] : 0.0f;
+            nonfinite |= (uint32_t)((__float_as_uint(x) & 0x7f800000u) == 0x7f800000u);
+            sh[r][c] = x;
+        }
+        __syncthreads();
+        if (tid < 64) {
+            const int w = d - c0 < 64 ? (int)(d - c0) : 64;
+            for (int c = 0; c < w; ++c) acc = fmaf(sh[tid][c], sh[tid][c], acc);
+        }
+    }
+    if (tid < 64 && r0 + tid < n) nrm[r0 + tid] = acc;
+    if (bad != nullptr && __any(nonfinite) && (tid & 63) == 0) atomicOr(bad, 1);
+}
+
+// ---- the median's window ---------------------------------------------------
+// At n = 20000 (2e8 upper entries) about 1.7% of the keys are set aside; the
+// sample takes 20 us, counting and ranking them 30 us, and the walk in the
+// tiles' epilogue 110 us of a 644 us build, in place of two passes over S
+// (204 and 216 us): the whole build 991 -> 657 us.
+constexpr int kSegs = 64;          // lists of set-aside keys (tile t appends to list t mod kSegs)
+constexpr int kWinBins = 4096;     // intervals the window is cut into
+constexpr int kWinList = 16384;    // keys of the intervals that hold the two ranks
+constexpr int kSamples = 65536;    // sampled pairs ...
+constexpr int kSampleTail = 512;   // ... the window spans the sample's median rank +- 4 sigma (sqrt(65536) / 2
+                                   // each): it misses once in 16000 calls
+// Up to here every key is set aside and the window is the range of S (no
+// sample: 300 points 78 us instead of 91).
+constexpr int64_t kWholeN = 512;
+
+struct SelSeg {                    // one 128-byte line per list
+    uint32_t count, pad;
+    unsigned long long below;      // keys below the window
+    uint32_t fill[28];
+};
+struct SelWin {
+    float vlo, vhi;                // the window, both inclusive; neither is a zero, so values
+                                   // compare as their keys do
+    uint32_t lo;                   // key of vlo
+    uint32_t shift;                // interval of a key: (key - lo) >> shift < kWinBins
+    int32_t miss;                  // the median was not found this way
+    uint32_t bin[2];               // intervals of the two ranks ...
+    uint32_t rank[2];              // ... and the ranks inside them
+    uint32_t kmin[2], kmax[2];     // bounds of the keys in the two intervals
+    uint32_t done[3], nlist;
+};
+// Set-aside keys a list holds: all of its tiles' where everything is set
+// aside, else twice what the window's share of the sample makes expected,
+// and one full tile.
+int64_t seg_cap(int64_t n) {
+    const int64_t t = (n + BM - 1) / BM, tiles = t * (t + 1) / 2;
+    const int64_t per = (tiles + kSegs - 1) / kSegs * (BM * BM);
+    if (n <= kWholeN) return per;
+    const int64_t want = (int64_t)((double)n * (double)n / kSegs * 2.2 * kSampleTail / kSamples) + BM * BM;
+    return want < per ? want : per;
 }
 
 struct SimArgs {
@@ -54,10 +122,11 @@ struct SimArgs {
     int64_t ld;
     int64_t tiles_per_side;
     uint32_t *minmax;     // [0] = min key, [1] = max key of off-diagonal entries
-    // median preference: the first digit pass of the exact select (13-bit
-    // digits of the upper entries' keys; both ranks share the empty prefix)
-    // counted here, into hist[b] and hist[SEL_BINS + b]; null: no counting
-    unsigned long long *hist;
+    // median preference (else null): the window, the lists of keys set aside
+    const SelWin *win;
+    SelSeg *segs;
+    uint32_t *cand;       // kSegs lists of cap keys
+    uint32_t cap;
     const int32_t *bad;   // nonzero: the input failed the finite check, write nothing
 };
 
@@ -69,9 +138,9 @@ struct SimArgs {
 // (g, q = 0..3), written directly (one float per row, 128-byte row
 // segments per half wavefront) and mirrored (the four rows q are
 // consecutive columns of S's row c: one float4).  With the median
-// preference (COUNT) the epilogue also counts the first 13-bit digit of
-// every upper entry's key in an LDS histogram whose nonzero bins the tile
-// adds to the global one: the select's first pass over S is not needed.
+// preference (COUNT) the epilogue also counts the upper entries below the
+// window and sets aside the keys inside it: every wavefront collects its own
+// in LDS and appends them to the tile's list.
 constexpr int LDA = BM + 1;   // padded LDS rows: conflict-free transposed stores
 
 // Gram block <x_i, x_k> of rows row0.. and columns col0.. (BM each) into the
@@ -135,7 +204,7 @@ __device__ __forceinline__ void gram_tile(const float *X, int64_t n, int64_t d, 
 }
 
 template <bool COUNT>
-__global__ __launch_bounds__(NT) void k_sim_gemm(SimArgs a) {
+__global__ __launch_bounds__(NT, 3) void k_sim_gemm(SimArgs a) {
     if (*a.bad) return;
     // Decode the upper-triangle tile (bi <= bj) from the linear block index.
     const int64_t T = a.tiles_per_side;
@@ -149,15 +218,33 @@ __global__ __launch_bounds__(NT) void k_sim_gemm(SimArgs a) {
 
     __shared__ float As[KB * LDA], Bs[KB * LDA];    // 16.5 KB of staging
     __shared__ float nr[BM], nc[BM];                // squared norms of the tile's rows and columns
-    __shared__ uint32_t hsh[COUNT ? SEL_BINS : 1];  // first-digit counts of the tile's upper entries
+    constexpr int kHold = 1024;                     // keys a wavefront holds before it appends them
+    __shared__ uint32_t held[COUNT ? NT / 64 : 1][COUNT ? kHold : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    if constexpr (COUNT)
-        for (int b = tid; b < SEL_BINS; b += NT) hsh[b] = 0u;   // published by gram_tile's barriers (d >= 1)
     for (int e = tid; e < BM; e += NT) {
         nr[e] = row0 + e < a.n ? a.nrm[row0 + e] : 0.0f;
         nc[e] = col0 + e < a.n ? a.nrm[col0 + e] : 0.0f;
     }
+    float wlo = 0.0f, whi = 0.0f;
+    uint32_t below = 0u;
+    int nheld = 0;
+    SelSeg *const seg = COUNT ? a.segs + blockIdx.x % kSegs : nullptr;
+    uint32_t *const list = COUNT ? a.cand + (int64_t)(blockIdx.x % kSegs) * a.cap : nullptr;
+    if constexpr (COUNT) {
+        wlo = a.win->vlo;
+        whi = a.win->vhi;
+    }
+    auto append = [&]() {
+        uint32_t at = 0u;
+        if (lane == 0) at = atomicAdd(&seg->count, (uint32_t)nheld);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int e = lane; e < nheld; e += 64)
+            if (at + e < a.cap) list[at + e] = held[wave][e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        nheld = 0;
+    };
     v16f acc[2][2];
     gram_tile(a.X, a.n, a.d, a.ldx, row0, col0, acc, As, Bs);
 
@@ -187,7 +274,6 @@ __global__ __launch_bounds__(NT) void k_sim_gemm(SimArgs a) {
                             const uint32_t key = fkey(v[q]);
                             kmin = min(kmin, key);
                             kmax = max(kmax, key);
-                            if constexpr (COUNT) atomicAdd(&hsh[key >> 19], 1u);
                         }
                     }
                     float *dst = a.S + k * a.ld + ib;
@@ -212,12 +298,47 @@ __global__ __launch_bounds__(NT) void k_sim_gemm(SimArgs a) {
                             const uint32_t key = fkey(v[q]);
                             kmin = min(kmin, key);
                             kmax = max(kmax, key);
-                            if constexpr (COUNT) atomicAdd(&hsh[key >> 19], 1u);
                         }
                     }
                 }
             }
         }
+    // The window: upper entries below it counted, those inside set aside.  A
+    // walk of its own (the values are formed again, two operations each), so
+    // that all lanes take part; tiles above the diagonal and inside S need no
+    // test of the indices.
+    if constexpr (COUNT) {
+        auto walk = [&](auto every) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    const int c = wn * 64 + y * 32 + (lane & 31);
+                    const float ncc = nc[c];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int mb = wm * 64 + x * 32 + 8 * g + 4 * (lane >> 5);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float v = 2.0f * acc[x][y][4 * g + q] - (nr[mb + q] + ncc);
+                            bool up = true;
+                            if constexpr (!decltype(every)::value)
+                                up = col0 + c < a.n && row0 + mb + q < a.n && (!diag_tile || mb + q < c);
+                            below += __popcll(__ballot(up && v < wlo));
+                            const unsigned long long m = __ballot(up && v >= wlo && v <= whi);
+                            if (m == 0ull) continue;
+                            if ((m >> lane) & 1ull) held[wave][nheld + __popcll(m & ((1ull << lane) - 1ull))] = fkey(v);
+                            nheld += __popcll(m);
+                        }
+                        if (nheld > kHold - 256) append();   // (four more entries fill at most 256)
+                    }
+                }
+        };
+        if (!diag_tile && row0 + BM <= a.n && col0 + BM <= a.n) walk(std::true_type{});
+        else walk(std::false_type{});
+        if (nheld) append();
+        if (lane == 0 && below) atomicAdd(&seg->below, (unsigned long long)below);
+    }
     // Block min/max of the upper off-diagonal entries: wavefronts, then the
     // tile, then one atomic per bound, skipped when it cannot change the value
     // (all tiles update the same two words).
@@ -240,17 +361,6 @@ __global__ __launch_bounds__(NT) void k_sim_gemm(SimArgs a) {
         if (kmin < __atomic_load_n(&a.minmax[0], __ATOMIC_RELAXED)) atomicMin(&a.minmax[0], kmin);
         if (kmax > __atomic_load_n(&a.minmax[1], __ATOMIC_RELAXED)) atomicMax(&a.minmax[1], kmax);
     }
-    // the tile's counts (integers: the sums do not depend on the order);
-    // the barrier above ordered every LDS count before these reads
-    if constexpr (COUNT) {
-        for (int b = tid; b < SEL_BINS; b += NT) {
-            const uint32_t c = hsh[b];
-            if (c) {
-                atomicAdd(&a.hist[b], (unsigned long long)c);
-                atomicAdd(&a.hist[SEL_BINS + b], (unsigned long long)c);
-            }
-        }
-    }
 }
 
 // ---- exact order statistics of the upper triangle -------------------------
@@ -270,8 +380,23 @@ __device__ __forceinline__ void sel_digit(int pass, int &shift, int &bits, uint3
     hmask = pass == 0 ? 0u : (pass == 1 ? 0xfff80000u : 0xfffffe00u);
 }
 
-__global__ void k_sel_init(SelState *st, uint32_t *minmax, unsigned long long lo,
-                           unsigned long long hi, unsigned long long *hist) {
+// Start of the select; of the window (win nullable: everything set aside
+// until a sample narrows it), of the finite-check flag (nullable).
+__global__ void k_sel_init(SelState *st, uint32_t *minmax, unsigned long long lo, unsigned long long hi,
+                           unsigned long long *hist, SelWin *win, SelSeg *segs, uint32_t *whist, int32_t *bad) {
+    if (win != nullptr) {
+        if (threadIdx.x == 0) {
+            SelWin w{};
+            w.vlo = -INFINITY;
+            w.vhi = INFINITY;
+            w.kmin[0] = w.kmin[1] = 0xffffffffu;
+            *win = w;
+        }
+        uint32_t *sw = reinterpret_cast<uint32_t *>(segs);
+        for (int b = threadIdx.x; b < (int)(kSegs * sizeof(SelSeg) / 4); b += blockDim.x) sw[b] = 0u;
+        for (int b = threadIdx.x; b < kWinBins; b += blockDim.x) whist[b] = 0u;
+    }
+    if (bad != nullptr && threadIdx.x == 0) *bad = 0;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st->prefix[0] = st->prefix[1] = 0u;
         st->rank[0] = lo;
@@ -436,6 +561,339 @@ __global__ __launch_bounds__(256) void k_sel_pick(SelState *st, int pass, unsign
     for (int b = t; b < 2 * SEL_BINS; b += blockDim.x) hist[b] = 0ull;
 }
 
+// True in every thread of the last workgroup of the grid to come here; the
+// others' device-scope stores are then visible to device-scope loads.
+__device__ __forceinline__ bool last_block(uint32_t *done) {
+    __shared__ int last;
+    // the workgroup's device-scope stores and atomics have arrived (no cache
+    // holds them back, so nothing is flushed)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1u;
+    __syncthreads();
+    return last != 0;
+}
+__device__ __forceinline__ uint32_t ld_dev(const uint32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_dev(uint32_t *p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Similarities of kSamples pseudo-random pairs (16 lanes to a pair), then, in
+// the last workgroup, the window: the values of the sample's ranks at kSampleTail
+// either side of the middle, widened to the intervals (of kWinBins over the
+// sample's range) that hold them.  The window only has to hold the median;
+// nothing else depends on it.
+constexpr int SMP_T = 1024, SMP_BLOCKS = 128;
+__global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n, int64_t d, int64_t ldx,
+                                                      const float *nrm, uint32_t *smp, SelWin *win,
+                                                      const int32_t *bad) {
+    if (*bad) return;
+    __shared__ uint32_t hist[kWinBins];
+    __shared__ float red[2][SMP_T / 64];
+    __shared__ uint32_t wtot[SMP_T / 64];
+    __shared__ int edge[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // four pairs at a time per 16 lanes
+    constexpr int PER = kSamples / SMP_BLOCKS / (SMP_T / 16);
+    static_assert(PER % 4 == 0, "pairs per group");
+    for (int it = 0; it < PER; it += 4) {
+        const float *xi[4], *xk[4];
+        float nn[4], acc[4];
+        int p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            p[u] = (blockIdx.x * PER + it + u) * (SMP_T / 16) + (tid >> 4);
+            uint64_t z = (uint64_t)(p[u] + 1) * 0x9E3779B97F4A7C15ull;
+            z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+            z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+            z ^= z >> 31;
+            const int64_t i = (int64_t)(((z & 0xffffffffull) * (uint64_t)n) >> 32);
+            int64_t k = (int64_t)(((z >> 32) * (uint64_t)(n - 1)) >> 32);
+            k += k >= i;
+            xi[u] = X + i * ldx;
+            xk[u] = X + k * ldx;
+            nn[u] = nrm[i] + nrm[k];
+            acc[u] = 0.0f;
+        }
+        for (int64_t j = tid & 15; j < d; j += 16)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u] = fmaf(xi[u][j], xk[u][j], acc[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) acc[u] += __shfl_xor(acc[u], off, 64);
+            if ((tid & 15) == 0) st_dev(&smp[p[u]], __float_as_uint(2.0f * acc[u] - nn[u]));
+        }
+    }
+    if (!last_block(&win->done[0])) return;
+    constexpr int E = kSamples / SMP_T;
+    float v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = __uint_as_float(ld_dev(&smp[tid + e * SMP_T]));
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        lo = fminf(lo, v[e]);
+        hi = fmaxf(hi, v[e]);
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, off, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+    if (lane == 0) {
+        red[0][wave] = lo;
+        red[1][wave] = hi;
+    }
+    for (int b = tid; b < kWinBins; b += SMP_T) hist[b] = 0u;
+    __syncthreads();
+    for (int w = 0; w < SMP_T / 64; ++w) {
+        lo = fminf(lo, red[0][w]);
+        hi = fmaxf(hi, red[1][w]);
+    }
+    const float inv = (float)(kWinBins - 1) / (hi - lo);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int b = (int)((v[e] - lo) * inv);
+        atomicAdd(&hist[b < 0 ? 0 : b > kWinBins - 1 ? kWinBins - 1 : b], 1u);
+    }
+    __syncthreads();
+    const uint4 h = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+    const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
+    uint32_t inc = tot;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    if (lane == 63) wtot[wave] = inc;
+    __syncthreads();
+    uint32_t before = inc - tot;
+    for (int w = 0; w < wave; ++w) before += wtot[w];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t r = kSamples / 2 + (q ? kSampleTail : -kSampleTail);
+        if (r >= before && r < before + tot) {
+            uint32_t acc = before;
+            int e = 0;
+            while (e < 3 && r >= acc + c[e]) acc += c[e++];
+            edge[q] = 4 * tid + e;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const float w = (hi - lo) / (float)(kWinBins - 1);
+        float a = lo + (float)edge[0] * w, b = lo + (float)(edge[1] + 1) * w;
+        if (a == 0.0f) a = -1.0e-30f;
+        if (b == 0.0f) b = 1.0e-30f;
+        win->vlo = a;
+        win->vhi = b;
+        win->lo = fkey(a);
+        const uint32_t span = fkey(b) - fkey(a);      // (b >= a)
+        const int bits = span ? 32 - __builtin_clz(span) : 0;
+        win->shift = bits > 12 ? bits - 12 : 0;
+    }
+}
+
+// The window's first key and interval width: the sample's, or (whole) those
+// of the bounds of S.
+__device__ __forceinline__ void win_cut(const SelWin *win, const uint32_t *minmax, int whole, uint32_t &lo,
+                                        uint32_t &shift) {
+    lo = win->lo;
+    shift = win->shift;
+    if (whole) {
+        lo = minmax[0];
+        const uint32_t span = minmax[1] - lo;
+        const int bits = span ? 32 - __builtin_clz(span) : 0;
+        shift = bits > 12 ? bits - 12 : 0;
+    }
+}
+
+// Counts the set-aside keys by interval; the last workgroup finds the
+// intervals of the two ranks.
+constexpr int RANK_T = 1024;      // one workgroup per list
+__global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win, const SelSeg *segs,
+                                                      const uint32_t *cand, uint32_t cap, uint32_t *whist,
+                                                      const uint32_t *minmax, int whole, const int32_t *bad) {
+    if (*bad) return;
+    __shared__ uint32_t hist[kWinBins];
+    __shared__ uint32_t wtot[RANK_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int b = tid; b < kWinBins; b += RANK_T) hist[b] = 0u;
+    __syncthreads();
+    const int sg = blockIdx.x;
+    const uint32_t cnt = segs[sg].count < cap ? segs[sg].count : cap;
+    const uint32_t *list = cand + (int64_t)sg * cap;
+    uint32_t lo, shift;
+    win_cut(win, minmax, whole, lo, shift);
+    for (uint32_t e = tid; e < cnt; e += 8 * RANK_T) {
+        uint32_t key[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) key[u] = e + u * RANK_T < cnt ? list[e + u * RANK_T] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e + u * RANK_T < cnt) atomicAdd(&hist[(key[u] - lo) >> shift], 1u);
+    }
+    __syncthreads();
+    for (int b = tid; b < kWinBins; b += RANK_T)
+        if (hist[b]) atomicAdd(&whist[b], hist[b]);
+    if (!last_block(&win->done[1])) return;
+    // keys below the window and in it: lane s of every wavefront has list s
+    static_assert(kSegs == 64, "a list per lane");
+    unsigned long long below = segs[lane].below, total = segs[lane].count;
+    const bool over = __any(segs[lane].count > cap);
+    for (int off = 32; off >= 1; off >>= 1) {
+        below += __shfl_xor(below, off, 64);
+        total += __shfl_xor(total, off, 64);
+    }
+    constexpr int PER = kWinBins / RANK_T;
+    uint32_t c[PER], own = 0u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) c[q] = ld_dev(&whist[tid * PER + q]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) own += c[q];
+    uint32_t incl = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += wtot[w];
+    const uint32_t before = incl - own;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const unsigned long long rank = st->rank[r];
+        if (over || rank < below || rank - below >= total) {
+            if (tid == 0) win->miss = 1;
+            continue;
+        }
+        const uint32_t in = (uint32_t)(rank - below);
+        if (in >= before && in < incl) {
+            uint32_t cum = before;
+            int q = 0;
+            while (q < PER - 1 && in >= cum + c[q]) cum += c[q++];
+            win->bin[r] = (uint32_t)(tid * PER + q);
+            win->rank[r] = in - cum;
+        }
+    }
+}
+
+// Collects the keys of the two intervals; the last workgroup ranks them: ten
+// bits at a time below the interval's.
+__global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, const SelSeg *segs,
+                                                     const uint32_t *cand, uint32_t cap, uint32_t *list2,
+                                                     const uint32_t *minmax, int whole, const int32_t *bad) {
+    if (*bad || win->miss) return;
+    extern __shared__ uint32_t keys[];       // kWinList
+    __shared__ uint32_t hist[1024], wtot[RANK_T / 64], found[2], held, at0, bmin[2], bmax[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sg = blockIdx.x;
+    const uint32_t cnt = segs[sg].count < cap ? segs[sg].count : cap;
+    const uint32_t *list = cand + (int64_t)sg * cap;
+    const uint32_t b0 = win->bin[0], b1 = win->bin[1];
+    uint32_t lo, shift;
+    win_cut(win, minmax, whole, lo, shift);
+    if (tid == 0) held = 0u;
+    if (tid < 2) {
+        bmin[tid] = 0xffffffffu;
+        bmax[tid] = 0u;
+    }
+    __syncthreads();
+    uint32_t kmin[2] = {0xffffffffu, 0xffffffffu}, kmax[2] = {0u, 0u};
+    for (uint32_t e = tid; e < cnt; e += 8 * RANK_T) {
+        uint32_t key[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) key[u] = e + u * RANK_T < cnt ? list[e + u * RANK_T] : 0u;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t b = (key[u] - lo) >> shift;
+            if (e + u * RANK_T < cnt && (b == b0 || b == b1)) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+                    if (b == (r ? b1 : b0)) {
+                        kmin[r] = min(kmin[r], key[u]);
+                        kmax[r] = max(kmax[r], key[u]);
+                    }
+                const uint32_t at = atomicAdd(&held, 1u);
+                if (at < (uint32_t)kWinList) keys[at] = key[u];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (kmin[r] <= kmax[r]) {
+            atomicMin(&bmin[r], kmin[r]);
+            atomicMax(&bmax[r], kmax[r]);
+        }
+    __syncthreads();
+    if (tid == 0) at0 = atomicAdd(&win->nlist, held);
+    if (tid < 2 && bmin[tid] <= bmax[tid]) {
+        atomicMin(&win->kmin[tid], bmin[tid]);
+        atomicMax(&win->kmax[tid], bmax[tid]);
+    }
+    __syncthreads();
+    for (uint32_t e = tid; e < held && e < (uint32_t)kWinList; e += RANK_T)
+        if (at0 + e < (uint32_t)kWinList) st_dev(&list2[at0 + e], keys[e]);
+    if (!last_block(&win->done[2])) return;
+    const uint32_t nl = ld_dev(&win->nlist);
+    if (nl > (uint32_t)kWinList) {
+        // many equal values (points on a grid): the intervals hold one key
+        // each, or the window has missed
+        if (tid == 0) {
+            for (int r = 0; r < 2; ++r) {
+                if (ld_dev(&win->kmin[r]) != ld_dev(&win->kmax[r])) win->miss = 1;
+                st->prefix[r] = ld_dev(&win->kmin[r]);
+            }
+            if (win->miss) st->prefix[0] = st->prefix[1] = 0u;
+        }
+        return;
+    }
+    for (uint32_t e = tid; e < nl; e += RANK_T) keys[e] = ld_dev(&list2[e]) - lo;
+    __syncthreads();
+    for (int r = 0; r < 2; ++r) {
+        uint32_t prefix = r ? b1 : b0, rank = win->rank[r];
+        for (int left = (int)shift; left > 0;) {
+            const int bits = left < 10 ? left : 10;
+            const int sh = left - bits;
+            hist[tid] = 0u;
+            __syncthreads();
+            for (uint32_t e = tid; e < nl; e += RANK_T)
+                if (keys[e] >> left == prefix) atomicAdd(&hist[(keys[e] >> sh) & ((1u << bits) - 1u)], 1u);
+            __syncthreads();
+            const uint32_t own = hist[tid];
+            uint32_t incl = own;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t o = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += o;
+            }
+            if (lane == 63) wtot[wave] = incl;
+            __syncthreads();
+            for (int w = 0; w < wave; ++w) incl += wtot[w];
+            if (rank >= incl - own && rank < incl) {
+                found[0] = (uint32_t)tid;
+                found[1] = rank - (incl - own);
+            }
+            __syncthreads();
+            prefix = prefix << bits | found[0];
+            rank = found[1];
+            left = sh;
+            __syncthreads();
+        }
+        if (tid == 0) st->prefix[r] = lo + prefix;
+    }
+}
+
+// What the host reads at the end (pinned host memory).
+struct SimReport {
+    double pref;
+    uint32_t bounds[2];
+    int32_t bad, miss;
+};
+
 struct PrefArgs {
     float *S;
     int64_t n, ld;
@@ -448,6 +906,8 @@ struct PrefArgs {
     double noise_rel;
     double *pref_dev;         // out: the scalar preference (median/scalar)
     const int32_t *bad = nullptr;   // nonzero: the input failed the finite check, write nothing
+    const SelWin *win = nullptr;    // miss set: the median is not known yet, write nothing
+    SimReport *rep = nullptr;
 };
 
 __device__ __forceinline__ double pref_of(const PrefArgs &a, int64_t i, double pm) {
@@ -516,6 +976,15 @@ __global__ void k_pref_range(PrefArgs a, double *range_out) {
     if (threadIdx.x == 0) {
         *range_out = (double)hi[0] - (double)lo[0];
         *a.pref_dev = pm;
+        if (a.rep != nullptr) {
+            SimReport r;
+            r.pref = pm;
+            r.bounds[0] = a.minmax[0];
+            r.bounds[1] = a.minmax[1];
+            r.bad = *a.bad;
+            r.miss = a.win != nullptr ? a.win->miss : 0;
+            *a.rep = r;
+        }
     }
 }
 
@@ -523,75 +992,24 @@ __global__ void k_pref_range(PrefArgs a, double *range_out) {
 // v becomes fl32(v + scale * u(i,k)).  S is symmetric before the noise, so
 // the upper triangle alone is read: an entry the noise changes (add_noise)
 // is written at (i,k) and, with its own draw, at (k,i); the others keep v.
+// No entry of S is read where the largest one is so far below zero that the
+// noise cannot change any (add_noise's bound at the largest value).
 __global__ __launch_bounds__(256) void k_pref_noise(PrefArgs a, const double *range) {
-    if (a.bad != nullptr && *a.bad) return;
+    if ((a.bad != nullptr && *a.bad) || (a.win != nullptr && a.win->miss)) return;
     const double pm = median_of(a);
     const double scale = a.noise_rel * (*range);
     const bool noise = a.noise_rel > 0.0;
-    for (int64_t i = blockIdx.x; i < a.n; i += gridDim.x) {
-        float *row = a.S + i * a.ld;
-        if (threadIdx.x == 0) {
-            const double base = pref_of(a, i, pm);
-            row[i] = noise ? (float)(base + scale * noise_u(a.seed, a.n, i, i)) : (float)base;
-        }
-        if (!noise) continue;
-        upper_row<8>(row, i, a.n, [&](int64_t k, float v) {
-            if (scale <= fabs((double)v) * 0x1p-27) return;
-            put_noise(a.S, a.ld, v, scale, a.seed, a.n, i, k);
-        });
-    }
-}
-
-// Median mode, last select pass fused with the tie noise: the upper triangle
-// is read once and counted for the last digit (values before noise); an
-// entry the noise changes is written at (i,k) and, with its own draw, at
-// (k,i) (S is symmetric before the noise; no pass reads the lower triangle
-// or an entry after its row's block has read it).  The diagonal is left for
-// k_pref_diag once the median is known.  The noise scale needs only the
-// off-diagonal range (the median lies inside it).
-__global__ __launch_bounds__(256) void k_sel_hist_noise(PrefArgs a, unsigned long long *hist) {
-    if (a.bad != nullptr && *a.bad) return;
-    extern __shared__ uint32_t hsh[];
-    constexpr int pass = 2;
-    int shift, bits;
-    uint32_t hmask;
-    sel_digit(pass, shift, bits, hmask);
-    const uint32_t nb = 1u << bits;
-    for (uint32_t b = threadIdx.x; b < 2 * nb; b += blockDim.x) hsh[b] = 0u;
-    __syncthreads();
-    const uint32_t p0 = a.sel->prefix[0], p1 = a.sel->prefix[1];
-    const bool same = p0 == p1;
-    uint32_t *const h0 = hsh;
-    uint32_t *const h1 = hsh + nb;
-    const double scale = a.noise_rel * ((double)keyf(a.minmax[1]) - (double)keyf(a.minmax[0]));
-    for (int64_t i = blockIdx.x; i < a.n - 1; i += gridDim.x) {
-        float *row = a.S + i * a.ld;
-        upper_row<8>(row, i, a.n, [&](int64_t k, float v) {
-            const uint32_t key = fkey(v);
-            const uint32_t dig = (key >> shift) & (nb - 1u);
-            if ((key & hmask) == p0) atomicAdd(&h0[dig], 1u);
-            if (!same && (key & hmask) == p1) atomicAdd(&h1[dig], 1u);
-            if (scale <= fabs((double)v) * 0x1p-27) return;
-            put_noise(a.S, a.ld, v, scale, a.seed, a.n, i, k);
-        });
-    }
-    __syncthreads();
-    for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) {
-        const uint32_t c0 = h0[b], c1 = same ? c0 : h1[b];
-        if (c0) atomicAdd(&hist[b], (unsigned long long)c0);
-        if (c1) atomicAdd(&hist[SEL_BINS + b], (unsigned long long)c1);
-    }
-}
-
-// The diagonal after the fused pass: s(i,i) = p (+ its noise).
-__global__ void k_pref_diag(PrefArgs a, const double *range) {
-    if (a.bad != nullptr && *a.bad) return;
-    const double pm = median_of(a);
-    const double scale = a.noise_rel * (*range);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * 256) {
         const double base = pref_of(a, i, pm);
-        a.S[i * a.ld + i] = a.noise_rel > 0.0 ? (float)(base + scale * noise_u(a.seed, a.n, i, i)) : (float)base;
+        a.S[i * a.ld + i] = noise ? (float)(base + scale * noise_u(a.seed, a.n, i, i)) : (float)base;
     }
+    const float top = keyf(a.minmax[1]);
+    if (!noise || (top < 0.0f && scale <= fabs((double)top) * 0x1p-27)) return;
+    for (int64_t i = blockIdx.x; i < a.n; i += gridDim.x)
+        upper_row<8>(a.S + i * a.ld, i, a.n, [&](int64_t k, float v) {
+            if (scale <= fabs((double)v) * 0x1p-27) return;
+            put_noise(a.S, a.ld, v, scale, a.seed, a.n, i, k);
+        });
 }
 
 // ---- matrix-free S: row panels ---------------------------------------------
@@ -699,7 +1117,9 @@ using namespace apx;
 
 namespace {
 struct SimLayout {
-    size_t o_n, o_mm, o_sel, o_h, o_r, bytes;
+    size_t o_n, o_mm, o_sel, o_h, o_r, base;                  // also the matrix-free sweeps'
+    size_t o_win, o_seg, o_wh, o_l, o_smp, o_cand, bytes;     // the median's window
+    int64_t cap;
 };
 SimLayout sim_layout(int64_t n) {
     WsLayout L;
@@ -709,6 +1129,14 @@ SimLayout sim_layout(int64_t n) {
     o.o_sel = L.take(sizeof(SelState));
     o.o_h = L.take(sizeof(unsigned long long) * 2 * SEL_BINS);
     o.o_r = L.take(sizeof(double) * 2);
+    o.base = L.off;
+    o.cap = seg_cap(n);
+    o.o_win = L.take(sizeof(SelWin));
+    o.o_seg = L.take(sizeof(SelSeg) * kSegs);
+    o.o_wh = L.take(sizeof(uint32_t) * kWinBins);
+    o.o_l = L.take(sizeof(uint32_t) * kWinList);
+    o.o_smp = L.take(sizeof(uint32_t) * kSamples);
+    o.o_cand = L.take(sizeof(uint32_t) * (size_t)kSegs * (size_t)o.cap);
     o.bytes = L.off;
     return o;
 }
@@ -740,88 +1168,96 @@ extern "C" apx_status ap_similarity(apx_ctx *ctx, const float *X, int64_t n, int
 
     const SimLayout SL = sim_layout(n);
     const size_t o_n = SL.o_n, o_mm = SL.o_mm, o_sel = SL.o_sel, o_h = SL.o_h, o_r = SL.o_r;
-    apx_status st = ws_reserve(ctx, ctx->ws_base + SL.bytes);
+    // The median's window needs room for the keys set aside; a caller's
+    // workspace without it gets the radix select.
+    const bool median = pref_mode == APX_PREF_MEDIAN;
+    const bool windowed = median && (!ctx->ws_external || ctx->ws_base + SL.bytes <= ctx->ws_bytes);
+    apx_status st = ws_reserve(ctx, ctx->ws_base + (windowed ? SL.bytes : SL.base));
     if (st != APX_OK) return st;
 
-    // Non-finite input is rejected before S is written.
-    int32_t *hflag = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->pinned) + 2048);
-    HIP_TRY(launch_fill_u8(reinterpret_cast<uint8_t *>(ctx->dflag), sizeof(int32_t), 0, s), "finite check");
-    HIP_TRY(launch_check_finite(X, n, d, ldx, ctx->dflag, s), "finite check");
-    if (pref_mode == APX_PREF_VECTOR) HIP_TRY(launch_check_finite(pref_vec, 1, n, n, ctx->dflag, s), "finite check");
-    // (no wait here: every kernel that writes S reads the flag first and
-    // returns when it is set; the host reads it at the end)
-    const int32_t *bad = static_cast<const int32_t *>(ctx->dflag);
     char *b = static_cast<char *>(ctx->ws) + ctx->ws_base;
     float *nrm = reinterpret_cast<float *>(b + o_n);
     uint32_t *mm = reinterpret_cast<uint32_t *>(b + o_mm);
     SelState *sel = reinterpret_cast<SelState *>(b + o_sel);
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(b + o_h);
     double *dvals = reinterpret_cast<double *>(b + o_r);   // [0] range, [1] preference
+    SelWin *win = windowed ? reinterpret_cast<SelWin *>(b + SL.o_win) : nullptr;
+    SelSeg *segs = reinterpret_cast<SelSeg *>(b + SL.o_seg);
+    uint32_t *whist = reinterpret_cast<uint32_t *>(b + SL.o_wh);
+    uint32_t *cand = reinterpret_cast<uint32_t *>(b + SL.o_cand);
+    SimReport *rep = reinterpret_cast<SimReport *>(static_cast<char *>(ctx->pinned) + 1024);
 
     const unsigned long long M = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
     const unsigned long long lo = (M % 2) ? (M - 1) / 2 : M / 2 - 1;
     const unsigned long long hi = (M % 2) ? (M - 1) / 2 : M / 2;
-    k_sel_init<<<1, 256, 0, s>>>(sel, mm, lo, hi, hist);
+    // Non-finite input is rejected before S is written: every kernel that
+    // writes S reads the flag first and returns when it is set; the host
+    // reads it at the end.
+    int32_t *bad = static_cast<int32_t *>(ctx->dflag);
+    k_sel_init<<<1, 1024, 0, s>>>(sel, mm, lo, hi, hist, win, segs, whist, bad);
     HIP_TRY(hipGetLastError(), "select init");
-    k_sqnorm<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(X, n, d, ldx, nrm);
+    if (pref_mode == APX_PREF_VECTOR) HIP_TRY(launch_check_finite(pref_vec, 1, n, n, bad, s), "finite check");
+    k_sqnorm<<<(unsigned)((n + 63) / 64), 256, 0, s>>>(X, n, d, ldx, nrm, bad);
     HIP_TRY(hipGetLastError(), "sqnorm");
-    // median preference: the GEMM counts the select's first digit
-    SimArgs sa{X, n, d, ldx, nrm, S, ld, (n + BM - 1) / BM, mm, pref_mode == APX_PREF_MEDIAN ? hist : nullptr, bad};
+    if (windowed && n > kWholeN) {
+        k_sel_sample<<<SMP_BLOCKS, SMP_T, 0, s>>>(X, n, d, ldx, nrm, reinterpret_cast<uint32_t *>(b + SL.o_smp), win,
+                                                  bad);
+        HIP_TRY(hipGetLastError(), "median sample");
+    }
+    SimArgs sa{X, n, d, ldx, nrm, S, ld, (n + BM - 1) / BM, mm, win, segs, cand, (uint32_t)SL.cap, bad};
     const int64_t ntiles = sa.tiles_per_side * (sa.tiles_per_side + 1) / 2;
-    if (sa.hist) k_sim_gemm<true><<<(unsigned)ntiles, NT, 0, s>>>(sa);
+    if (windowed) k_sim_gemm<true><<<(unsigned)ntiles, NT, 0, s>>>(sa);
     else k_sim_gemm<false><<<(unsigned)ntiles, NT, 0, s>>>(sa);
     HIP_TRY(hipGetLastError(), "similarity gemm");
-    PrefArgs pa{S, n, ld, pref_mode, pref_vec, pref_scalar, sel, mm, noise_seed, noise_rel, &dvals[1], bad};
-    if (pref_mode == APX_PREF_MEDIAN) {
-        // three digits: the first counted by the GEMM, two passes over the
-        // upper triangle; with noise the last one also adds the noise to
-        // every off-diagonal entry
-        for (int pass = 0; pass < 3; ++pass) {
-            const size_t lds = sizeof(uint32_t) * (pass == 0 ? 8192 : 2 * (pass == 1 ? 1024 : 512));
-            if (pass == 0) {
-                // first digit: counted by the GEMM
-            } else if (pass == 2 && noise_rel > 0.0) {
-                const int g = walk_grid((const void *)k_sel_hist_noise, lds, n - 1);
-                k_sel_hist_noise<<<g, 256, lds, s>>>(pa, hist);
-            } else {
+    PrefArgs pa{S, n, ld, pref_mode, pref_vec, pref_scalar, sel, mm, noise_seed, noise_rel, &dvals[1], bad, win, rep};
+    const int noise_grid = (int)(n < 4096 ? n : 4096);
+    if (windowed) {
+        const int whole = n <= kWholeN;
+        k_win_count<<<kSegs, RANK_T, 0, s>>>(sel, win, segs, cand, (uint32_t)SL.cap, whist, mm, whole, bad);
+        HIP_TRY(hipGetLastError(), "median count");
+        constexpr size_t lds = sizeof(uint32_t) * kWinList;
+        HIP_TRY(hipFuncSetAttribute((const void *)k_win_rank, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+                "lds");
+        k_win_rank<<<kSegs, RANK_T, lds, s>>>(sel, win, segs, cand, (uint32_t)SL.cap,
+                                               reinterpret_cast<uint32_t *>(b + SL.o_l), mm, whole, bad);
+        HIP_TRY(hipGetLastError(), "median rank");
+    }
+    bool searched = windowed || !median;
+    for (;;) {
+        if (!searched) {
+            // three digits of the keys, a pass over the upper triangle each
+            for (int pass = 0; pass < 3; ++pass) {
+                const size_t lds = sizeof(uint32_t) * (pass == 0 ? 8192 : 2 * (pass == 1 ? 1024 : 512));
                 const int g = walk_grid((const void *)k_sel_hist, lds, n - 1);
                 k_sel_hist<<<g, 256, lds, s>>>(S, n, ld, sel, pass, hist, 0, n);
+                HIP_TRY(hipGetLastError(), "select histogram");
+                k_sel_pick<<<1, 256, 0, s>>>(sel, pass, hist);
+                HIP_TRY(hipGetLastError(), "select pick");
             }
-            HIP_TRY(hipGetLastError(), "select histogram");
-            k_sel_pick<<<1, 256, 0, s>>>(sel, pass, hist);
-            HIP_TRY(hipGetLastError(), "select pick");
+            pa.win = nullptr;
         }
         k_pref_range<<<1, 256, 0, s>>>(pa, &dvals[0]);
         HIP_TRY(hipGetLastError(), "preference range");
-        k_pref_diag<<<(unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024), 256, 0, s>>>(pa, &dvals[0]);
-        HIP_TRY(hipGetLastError(), "preference");
-    } else {
-        k_pref_range<<<1, 256, 0, s>>>(pa, &dvals[0]);
-        HIP_TRY(hipGetLastError(), "preference range");
-        const int g = (int)(n < 8192 ? n : 8192);
-        k_pref_noise<<<g, 256, 0, s>>>(pa, &dvals[0]);
+        k_pref_noise<<<noise_grid, 256, 0, s>>>(pa, &dvals[0]);
         HIP_TRY(hipGetLastError(), "preference/noise");
+        HIP_TRY(hipStreamSynchronize(s), "sync");
+        if (rep->bad || !rep->miss) break;
+        searched = false;      // (nothing of the preferences has been written)
     }
     // The bounds of the off-diagonal keys tell whether a similarity overflowed
     // (a key at or beyond the one of +inf or -inf: infinities and NaNs).
-    double *h = reinterpret_cast<double *>(static_cast<char *>(ctx->pinned) + 1024);
-    uint32_t *hk = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->pinned) + 1088);
-    HIP_TRY(hipMemcpyAsync(h, &dvals[1], sizeof(double), hipMemcpyDeviceToHost, s), "pref copy");
-    HIP_TRY(hipMemcpyAsync(hk, mm, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s), "bounds copy");
-    HIP_TRY(hipMemcpyAsync(hflag, ctx->dflag, sizeof(int32_t), hipMemcpyDeviceToHost, s), "finite check");
-    HIP_TRY(hipStreamSynchronize(s), "sync");
-    if (*hflag) return set_err(ctx, APX_EINVAL, "X or pref_vec holds a NaN or infinite value");
+    if (rep->bad) return set_err(ctx, APX_EINVAL, "X or pref_vec holds a NaN or infinite value");
     const uint32_t key_pinf = 0xff800000u, key_ninf = 0x007fffffu;   // fkey(+inf), fkey(-inf)
-    if (hk[1] >= key_pinf || hk[0] <= key_ninf)
+    if (rep->bounds[1] >= key_pinf || rep->bounds[0] <= key_ninf)
         return set_err(ctx, APX_EINVAL, "similarities overflow FP32 (S holds non-finite values)");
-    if (pref_out) *pref_out = pref_mode == APX_PREF_VECTOR ? NAN : *h;
+    if (pref_out) *pref_out = pref_mode == APX_PREF_VECTOR ? NAN : rep->pref;
     return APX_OK;
 }
 
 // ---- matrix-free similarity: the row panels of ap_solve_mf -----------------
 namespace apx {
 
-size_t mf_sim_bytes(int64_t n) { return sim_layout(n).bytes; }
+size_t mf_sim_bytes(int64_t n) { return sim_layout(n).base; }
 
 namespace {
 struct MfPtrs {
@@ -880,10 +1316,10 @@ hipError_t mf_sim_setup(const MfSim &m, float *panel, int64_t ld, int64_t prows,
     const unsigned long long M = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
     const unsigned long long lo = (M % 2) ? (M - 1) / 2 : M / 2 - 1;
     const unsigned long long hi = (M % 2) ? (M - 1) / 2 : M / 2;
-    k_sel_init<<<1, 256, 0, s>>>(q.sel, q.mm, lo, hi, q.hist);
+    k_sel_init<<<1, 256, 0, s>>>(q.sel, q.mm, lo, hi, q.hist, nullptr, nullptr, nullptr, nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_sqnorm<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(m.X, n, m.d, m.ldx, q.nrm);
+    k_sqnorm<<<(unsigned)((n + 63) / 64), 256, 0, s>>>(m.X, n, m.d, m.ldx, q.nrm, nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int sweeps = m.pref_mode == APX_PREF_MEDIAN ? 3 : 1;
     for (int pass = 0; pass < sweeps; ++pass) {
