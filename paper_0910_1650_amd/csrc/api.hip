@@ -396,11 +396,13 @@ apx_status resident_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, f
         return APX_ENOTIMPL;
     }
     HIP_TRY(hipStreamSynchronize(s), "sync");
-    if (!out->done) {
-        // a wait was given up: a cold start can begin again, a warm start may
-        // have lost its A_0 and R_0 to the rows already written
-        return warm == APX_COLD ? APX_ENOTIMPL
-                                : set_err(ctx, APX_EDEVICE, "a wait between workgroups timed out");
+    if (out->done != 1) {
+        // a wait was given up: before the first iteration (-1), or on a cold
+        // start, the run can begin again; later a warm start may have lost
+        // its A_0 and R_0 to the rows already written
+        return warm == APX_COLD || out->done < 0
+                   ? APX_ENOTIMPL
+                   : set_err(ctx, APX_EDEVICE, "a wait between workgroups timed out");
     }
     ctx->last_imp_iters = ctx->last_ia_iters = 0;
     ctx->last_exp_iters = out->iterations;

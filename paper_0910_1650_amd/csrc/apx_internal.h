@@ -235,7 +235,7 @@ constexpr int64_t kResMaxN = 3072;
 struct ResOut {
     double dpsim, expref;
     int32_t iterations, converged, n_exemplars;
-    int32_t done;        // 1 when the run ended by its stop rule
+    int32_t done;        // 1 when the run ended by its stop rule, -1 when a wait was given up before iteration 1
 };
 struct ResInst {
     const float *S;

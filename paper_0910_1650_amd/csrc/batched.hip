@@ -810,7 +810,7 @@ apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spe
         return hip_err(ctx, e, "batched launch");
     for (size_t q = 0; q < cnt; ++q) {
         const ResOut &o = out[q];
-        if (!o.done) return set_err(ctx, APX_EDEVICE, "batched launch: a wait between workgroups timed out");
+        if (o.done != 1) return set_err(ctx, APX_EDEVICE, "batched launch: a wait between workgroups timed out");
         apx_result &r = res[B.order[q]];
         std::memset(&r, 0, sizeof r);
         r.iterations = o.iterations;

@@ -600,7 +600,13 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         }
         if (tid == 0) L.cnt[nu ^ 1] = 0;
         __syncthreads();
-        if (*L.fail) return false;
+        if (*L.fail) {
+            // In the first exchange a member may not run yet, while other
+            // work holds the chip.  One that gives up there publishes no
+            // iteration 1, so no member ends and no row has been written.
+            if (first && tid == 0) d.out->done = -1;
+            return false;
+        }
         // the set of iteration t (none at t = 0) against the one before
         if (!first) run = (t > 1 && !L.cnt[nu]) ? run + 1 : 1;
     }
