@@ -160,7 +160,7 @@ def workload_extras(apx) -> dict:
 
     * pap_c3: Algorithm 2 on 40000 points on a union of 20 random 5-D
       subspaces of R^100, 8 random parts of 3000-7000 points; the parts'
-      sub-problems alone (one persistent batched launch) with their HBM rate
+      sub-problems alone (the batched solve) with their rate on 20 B
       (20 B per element and iteration of the explicit form those passes run,
       summed over the parts' own iteration counts), the whole pap_solve
       (parts of consecutive indices: Step 4 keeps A implicit; and the same
@@ -248,13 +248,14 @@ def workload_extras(apx) -> dict:
     b_gbs = b_bytes / (ms_b * 1e-3) / 1e9
     out["batch_512"] = {
         "workload": "512 independent 2-D Gaussian mixtures, n in [100, 2000], 2-20 components, "
-                    "median preference, damping 0.5, at most 200 iterations, one launch",
+                    "median preference, damping 0.5, at most 200 iterations, one call",
         "sum_n2": int(sum(S_.shape[0] ** 2 for S_ in Ss)),
         "ms": round(ms_b, 2), "instance_iterations": it_sum,
         "instance_iterations_per_s": round(it_sum / (ms_b * 1e-3), 1),
         "converged": int(sum(r.converged for r in rs)),
         "GBps": round(b_gbs, 1), "frac": round(b_gbs / HBM_PEAK_GBS, 4),
-        "bytes_basis": "20 B per element and iteration (explicit form), each instance's own count",
+        "bytes_basis": "20 B per element and iteration (explicit form), each instance's own count: the rate that "
+                       "form would need, not bytes moved (up to 3072 points the messages stay in registers)",
     }
     del Ss, Rs, As, idxs
     torch.cuda.empty_cache()

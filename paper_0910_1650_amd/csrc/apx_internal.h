@@ -307,7 +307,7 @@ struct TuneEntry {
     double form_ms[3] = {0.0, 0.0, 0.0};
 };
 int64_t tune_bucket(int64_t n);
-// Tuned plan of the persistent batched launch for batches of one shape
+// Tuned plan of the streaming batched launch for batches of one shape
 // (bit lengths of the instance count and of the largest n).
 struct BatchTune {
     int32_t count_bits, n_bits;
