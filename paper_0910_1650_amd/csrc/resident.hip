@@ -679,10 +679,11 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
             const v4f s4 = get_s(q, lr, j);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float v = m4[e] == 0.0f ? s4[e] : kNegInf;
-                if (v > best) {
-                    best = v;
-                    at = 4 * (64 * j + lane) + e;
+                // (an exemplar at -inf counts too: the lowest one, where no other is nearer)
+                const int k = 4 * (64 * j + lane) + e;
+                if (m4[e] == 0.0f && (s4[e] > best || (s4[e] == best && k < at))) {
+                    best = s4[e];
+                    at = k;
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
