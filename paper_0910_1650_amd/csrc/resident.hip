@@ -89,11 +89,19 @@ __device__ __forceinline__ void st_row(float *p, v4f v) { *(APX_GLOBAL v4f *)p =
 __device__ __forceinline__ float ld_one(const float *p) { return *(const APX_GLOBAL float *)p; }
 __device__ __forceinline__ void st_one(float *p, float v) { *(APX_GLOBAL float *)p = v; }
 
-// max(0, x) and max(a, b) as single instructions (the library functions
-// quiet a signalling NaN first, one more instruction per element)
+// max(0, x), min(0, x) and max(a, b) as single instructions (the library
+// functions quiet a signalling NaN first, one more instruction per element).
+// Of a number and a NaN all three give the number, like fmaxf and fminf: with
+// similarities of -inf a column sum can be +inf and t_k - max(0, r) then NaN.
+// minf is only for values that are no NaN.
 __device__ __forceinline__ float max0(float x) {
     float y;
     asm("v_max_f32 %0, 0, %1" : "=v"(y) : "v"(x));
+    return y;
+}
+__device__ __forceinline__ float min0(float x) {
+    float y;
+    asm("v_min_f32 %0, 0, %1" : "=v"(y) : "v"(x));
     return y;
 }
 __device__ __forceinline__ float maxf(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, INFINITY); }
@@ -211,7 +219,11 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
 
     // ---- the member's rows into registers.  The diagonal is kept apart; its
     // place and the padding columns hold s = r = -inf, which never wins a
-    // maximum and adds nothing to a column.
+    // maximum and adds nothing to a column.  A step of damping 0 makes their r
+    // 0 * -inf = NaN (with damping 0, or the first step from column-structured
+    // availabilities): max0 and maxf then give the other operand, as for a
+    // message that is NaN itself, no comparison with it holds, and it is never
+    // stored.
     float s[RPW][SR][4], r[RPW][EJ][4], a[RPW][EJ][4];
     float sd[RPW], rd[RPW], ad[RPW];
 #pragma unroll
@@ -289,7 +301,9 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
     const int slices = RT / rows;
     int rsc = (tid / rows) << 16 | (tid % rows);   // slice and column of this thread in exchange 1
 
-    for (int k = tid; k < NC; k += RT) L.t[k] = 0.0f;
+    // At t = 0 the availability step leaves A_0 as it is: t = +inf makes its
+    // update min(0, t - max(0, r)) zero whatever R_0 holds.
+    for (int k = tid; k < NC; k += RT) L.t[k] = INFINITY;
     for (int k = tid; k < kMaxRows; k += RT) {
         L.e[k] = 0;
         L.c[k] = 0.0f;
@@ -310,7 +324,12 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         float v1[RPW], v2[RPW], vd[RPW];
         int ex[RPW];
 #pragma unroll
-        for (int q = 0; q < RPW; ++q) v1[q] = v2[q] = kNegInf;
+        for (int q = 0; q < RPW; ++q) {
+            // Opaque: v_med3 of (v1, v2, NaN) is v2, but with a v2 known to be
+            // -inf the compiler makes it a minimum of v1 and NaN, which is v1.
+            v1[q] = v2[q] = kNegInf;
+            opaque(v2[q]);
+        }
         {
             float dv[RPW], D[RPW];
 #pragma unroll
@@ -330,7 +349,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float x = r[q][j][e];
-                        const float upd = minf(0.0f, t4[e] - max0(x));
+                        const float upd = min0(t4[e] - max0(x));
                         const float an = la * a[q][j][e] + oa * upd;
                         a[q][j][e] = an;
                         dv[q] = maxf(dv[q], an + x);
@@ -347,7 +366,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
                 const float w = wave_max(dv[q]);
                 const float dq = lane0(D[q]);
                 bool is = w < dq;
-                if (w == dq) {
+                if (w == dq && dq > kNegInf) {
                     // a tie goes to the lowest column: an exemplar unless a lower one reaches D
                     const int i = row0 + wave + q * RW;
                     bool lower = false;

@@ -25,10 +25,10 @@ def _neighbours_only(n, k, seed):
     return S
 
 
-def _solve(S, on, **kw):
+def _solve(S, on, start=None, **kw):
     apx.apx_set_graphs(on)
     try:
-        R, A = apx.empty_matrix(S.shape[0]), apx.empty_matrix(S.shape[0])
+        R, A = (apx.to_matrix(m) for m in start) if start else (apx.empty_matrix(S.shape[0]) for _ in "RA")
         idx, res = apx.ap_solve(S, R, A, **kw)
     finally:
         apx.apx_set_graphs(True)
@@ -62,3 +62,22 @@ def test_points_without_a_reachable_exemplar(n):
         assert (idx[lost] == int(ex[0])).all()
         cut_off += int(lost.sum())
     assert cut_off > 0
+
+
+@pytest.mark.parametrize("n", [40, 700, 2400])
+@pytest.mark.parametrize("damping", [0.0, 0.5])
+def test_points_with_one_neighbour_and_no_preference(n, damping):
+    """Preference -inf and a single neighbour: r(i,k) of that neighbour is
+    +inf, so its column's sum is too, and availabilities are min(0, inf - inf);
+    without damping 0 * inf makes further NaNs; a run can start from such messages."""
+    S = _neighbours_only(n, 4, n)
+    lone = torch.arange(0, n, 5)
+    best = S.clone().fill_diagonal_(-math.inf).max(1)
+    S[lone] = -math.inf
+    S[lone, best.indices[lone]] = best.values[lone]
+    M = apx.to_matrix(S)
+    for it in (1, 2, 5, 13):
+        _, _, R, A = _same(M, damping=damping, max_iter=it, conv_iter=0)
+        if damping:
+            assert (R[lone] == math.inf).any(1).all()
+            _same(M, warm=apx.APX_WARM_AR, start=(R, A), damping=damping, max_iter=3, conv_iter=0)
