@@ -235,7 +235,8 @@ __device__ __forceinline__ void row_tail(Each each, const uint32_t *keys, float 
 // (four passes, whose first digits are the exponent and put most of a row on
 // a few LDS counters) a row takes two passes over registers: 5000 rows of
 // 5000 85 us, 514 before.  A row whose values crowd (many ties: more than
-// kCand keys in the eleven intervals) is left to the radix select below.
+// kCand keys in the eleven intervals) is left to the radix select below, and
+// so is one that holds a value that is not finite.
 constexpr int ST_T = 512;
 constexpr int kBins = 2048, kCand = 1024;
 static_assert(kBins == 4 * ST_T, "four intervals per thread");
@@ -290,10 +291,13 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
             }
         };
         float lo = INFINITY, hi = -INFINITY;
+        bool nan = false;
         each([&](float x) {
             lo = fminf(lo, x);
             hi = fmaxf(hi, x);
+            nan |= x != x;
         });
+        if (nan) lo = -INFINITY;
         // over each 16 lanes (quad swaps, half-row and row mirrors)
         lo = fminf(lo, dpp_mov<0xB1>(lo)), hi = fmaxf(hi, dpp_mov<0xB1>(hi));
         lo = fminf(lo, dpp_mov<0x4E>(lo)), hi = fmaxf(hi, dpp_mov<0x4E>(hi));
@@ -313,6 +317,13 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
             const float4 b = *reinterpret_cast<const float4 *>(&bs.hi[4 * w]);
             lo = fminf(fminf(fminf(lo, a.x), fminf(a.y, a.z)), a.w);
             hi = fmaxf(fmaxf(fmaxf(hi, b.x), fmaxf(b.y, b.z)), b.w);
+        }
+        // A row that cannot be cut into equal widths (an infinity, a NaN, whose
+        // place is that of its key, a range beyond FP32) has no interval here.
+        if (!(hi - lo < INFINITY)) {
+            if (tid == 0) out[k].pad = 1;      // left to k_row_stats_radix
+            __syncthreads();
+            continue;
         }
         const float inv = (float)(kBins - 1) / (hi - lo);
         auto bin_of = [&](float x) -> int {

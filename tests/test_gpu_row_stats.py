@@ -32,3 +32,27 @@ def test_features_equal_oracle(n):
     np.testing.assert_array_equal(F.cpu().numpy()[rows], ref.astype(np.float32))
     med = np.sort(np.partition(S.cpu().numpy()[~np.eye(n, dtype=bool)].reshape(n, n - 1), (n - 2) // 2, axis=1)[:, (n - 2) // 2])
     assert float(sig) == abs(med[(n - 1) // 2])
+
+
+@pytest.mark.parametrize("n", [40, 700, 1500, 9000])
+def test_values_that_are_not_finite(n):
+    """Order statistics by the FP32 values' order with infinities at its ends
+    and NaN above them (as numpy sorts)."""
+    pts = synth.gaussian_mixture(n=n, d=8, k=5, seed=n)
+    S, _ = apx.ap_similarity(torch.from_numpy(pts.X).cuda(), noise_seed=1)
+    g = torch.Generator().manual_seed(n)
+    S[1, 5] = float("nan")
+    S[2, torch.randperm(n, generator=g)[:n // 3].cuda()] = float("nan")
+    S[3, 7:9] = -float("inf")
+    S[4, 7] = float("inf")
+    S[5, ::2] = -float("inf")
+    S[6, 9], S[6, 11], S[6, 12] = float("nan"), float("inf"), -float("inf")
+    S[7, 8], S[7, 9] = -3.0e38, 3.0e38
+    F, sig = apx.apx_features(S)
+    M, m = S.cpu().numpy(), n - 1
+    pos = [m - 1 - min(j, m - 1) for j in (0, 1, 3, 7, 15, 31)] + [q * (m - 1) // 100 for q in (1, 10, 25, 50, 75)]
+    for k in range(9):
+        row = np.sort(np.delete(M[k], k))
+        with np.errstate(invalid="ignore"):
+            ref = (row[pos].astype(np.float64) / float(sig)).astype(np.float32)
+        np.testing.assert_array_equal(F.cpu().numpy()[k, [0, 1, 2, 3, 4, 5, 7, 8, 9, 10, 11]], ref)
