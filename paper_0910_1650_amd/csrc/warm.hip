@@ -21,12 +21,13 @@
 //              column quantities.  R_0 = one undamped Eq. (2) step from A_0.
 //
 // Order statistics are exact: the keys of the eleven intervals of a row that
-// hold its ranks are collected and ranked by counting (k_row_stats); crowded
-// rows and the median of medians go through a most-significant-digit radix
-// select over the order-preserving integer image of the FP32 values (8-bit
-// digits, four passes).
+// hold its ranks are collected and ranked by counting (k_row_stats; crowded
+// rows by repeated cuts, k_row_stats_crowded); the median of medians goes
+// through a most-significant-digit radix select over the order-preserving
+// integer image of the FP32 values (8-bit digits, four passes).
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "apx_internal.h"
 
@@ -234,12 +235,43 @@ __device__ __forceinline__ void row_tail(Each each, const uint32_t *keys, float 
 // collected and ranked by counting.  Against the digits of a radix select
 // (four passes, whose first digits are the exponent and put most of a row on
 // a few LDS counters) a row takes two passes over registers: 5000 rows of
-// 5000 85 us, 514 before.  A row whose values crowd (many ties: more than
-// kCand keys in the eleven intervals) is left to the radix select below, and
+// 5000 85 us, 514 before.  A row whose values crowd (ties, a far outlier:
+// more than kCand keys in the eleven intervals, or many_keys in one, where
+// counting costs a multiple of the rest) is left to k_row_stats_crowded, and
 // so is one that holds a value that is not finite.
 constexpr int ST_T = 512;
 constexpr int kBins = 2048, kCand = 1024;
 static_assert(kBins == 4 * ST_T, "four intervals per thread");
+// Keys of an interval that are still ranked by counting (64: 2 us; 256: 25).
+// Evenly spread rows of 65536 points have about a hundred in one, and another
+// cut of such a row costs more than counting them.
+__device__ __forceinline__ int many_keys(int n) { return n > 64 * 512 ? n >> 9 : 64; }
+
+// Counts intervals one element at a time; MERGE (long rows, read again in
+// every pass): a thread's elements of one interval in a row are added at once,
+// so a crowded row does not wait for one LDS counter (20000 points, one of
+// them far out: 5.3 ms for all rows, 5.8 without).
+template <bool MERGE>
+struct Counter {
+    uint32_t *hist;
+    int at = -1;
+    uint32_t held = 0u;
+    __device__ __forceinline__ void add(int b) {
+        if constexpr (MERGE) {
+            if (b != at) {
+                if (held) atomicAdd(&hist[at], held);
+                at = b;
+                held = 0u;
+            }
+            ++held;
+        } else {
+            atomicAdd(&hist[b], 1u);
+        }
+    }
+    __device__ __forceinline__ void flush() {
+        if (MERGE && held) atomicAdd(&hist[at], held);
+    }
+};
 
 struct BinShared {
     uint32_t hist[kBins];
@@ -249,10 +281,95 @@ struct BinShared {
     int32_t bin[NTGT], rank[NTGT], cnt[NTGT];   // a rank's interval, its rank in it, the interval's keys
     int32_t off[NTGT];         // first key of a rank's list
     int32_t cursor[NTGT];      // by list
-    int32_t total;
+    int32_t total, most;       // keys of the lists, of the longest
     float lo[ST_T / 16], hi[ST_T / 16];
     uint32_t key[NTGT];
 };
+
+// From the counts of the intervals (bs.hist, complete): the interval, rank
+// inside it and list of every rank lane q of `want` asks for (lane < NTGT; a
+// rank beyond the counted keys is not looked up).  Ranks in one interval
+// share the list of the first of them.  Ends with a barrier.
+__device__ __forceinline__ void find_intervals(BinShared &bs, int32_t want) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    {
+        const uint4 h = *reinterpret_cast<const uint4 *>(&bs.hist[4 * tid]);
+        const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
+        uint32_t inc = tot;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += o;
+        }
+        if (lane == 63) bs.wtot[wave] = inc;
+        __syncthreads();
+        uint32_t before = inc - tot;
+        for (int w = 0; w < wave; ++w) before += bs.wtot[w];
+#pragma unroll
+        for (int q = 0; q < NTGT; ++q) {
+            const uint32_t r = (uint32_t)__builtin_amdgcn_readlane(want, q);
+            if (r >= before && r < before + tot) {
+                uint32_t acc = before;
+                int d = 0;
+                while (d < 3 && r >= acc + c[d]) acc += c[d++];
+                bs.bin[q] = 4 * tid + d;
+                bs.rank[q] = (int32_t)(r - acc);
+                bs.cnt[q] = (int32_t)c[d];
+            }
+        }
+    }
+    __syncthreads();
+    // one list per interval: lane q has rank q; equal intervals share the
+    // first one's list
+    if (wave == 0) {
+        const bool live = lane < NTGT && want >= 0;
+        const int b = live ? bs.bin[lane] : -1 - lane;
+        const int c = live ? bs.cnt[lane] : 0;
+        int first = lane;
+#pragma unroll
+        for (int q = NTGT - 1; q >= 0; --q)
+            if (__builtin_amdgcn_readlane(b, q) == b && q < first) first = q;
+        const bool own = live && first == lane;
+        int at = 0, total = 0, most = 0;
+#pragma unroll
+        for (int q = 0; q < NTGT; ++q) {
+            const int cq = __builtin_amdgcn_readlane(own ? c : 0, q);
+            if (q < first) at += cq;
+            total += cq;
+            most = cq > most ? cq : most;
+        }
+        if (lane < NTGT) bs.off[lane] = at;
+        if (own) {
+            bs.mark[b] = (uint8_t)(1 + lane);
+            bs.cursor[lane] = at;
+        }
+        if (lane == 0) {
+            bs.total = total;
+            bs.most = most;
+        }
+    }
+    __syncthreads();
+}
+
+// The keys of the ranks in `want` from their lists in bs.cand, by counting.
+__device__ __forceinline__ void rank_lists(BinShared &bs, int32_t want) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int q = wave; q < NTGT; q += ST_T / 64) {
+        if (__builtin_amdgcn_readlane(want, q) < 0) continue;
+        const uint32_t *l = bs.cand + bs.off[q];
+        const int c = bs.cnt[q], r = bs.rank[q];
+        for (int e = lane; e < c; e += 64) {
+            const uint32_t x = l[e];
+            int less = 0, same = 0;
+#pragma unroll 4
+            for (int i = 0; i < c; ++i) {
+                less += l[i] < x;
+                same += l[i] == x;
+            }
+            if (r >= less && r < less + same) bs.key[q] = x;   // (equal keys write the same)
+        }
+    }
+}
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x) {
@@ -264,10 +381,9 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
     __shared__ BinShared bs;
     __shared__ double wsum[ST_T / 64];
     __shared__ int32_t wcnt[ST_T / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int NW = ST_T / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int64_t m = n - 1;
-    const int32_t want = lane < NTGT ? stat_rank(lane, m) : 0;   // the ranks, lane by lane
+    const int32_t want = lane < NTGT ? stat_rank(lane, m) : -1;   // the ranks, lane by lane
     for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
         const float *row = S + k * ld;
         float v[E > 0 ? E : 1];
@@ -286,8 +402,17 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
                     if (j < n && j != (int)k) f(v[e]);
                 }
             } else {
-                for (int64_t j = tid; j < n; j += ST_T)
-                    if (j != k) f(row[j]);
+                // eight loads in flight (20000 points 1.69 -> 1.10 ms)
+                for (int j0 = tid; j0 < n; j0 += 8 * ST_T) {
+                    float x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = j0 + u * ST_T < n ? row[j0 + u * ST_T] : 0.0f;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int j = j0 + u * ST_T;
+                        if (j < n && j != (int)k) f(x[u]);
+                    }
+                }
             }
         };
         float lo = INFINITY, hi = -INFINITY;
@@ -319,9 +444,10 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
             hi = fmaxf(fmaxf(fmaxf(hi, b.x), fmaxf(b.y, b.z)), b.w);
         }
         // A row that cannot be cut into equal widths (an infinity, a NaN, whose
-        // place is that of its key, a range beyond FP32) has no interval here.
-        if (!(hi - lo < INFINITY)) {
-            if (tid == 0) out[k].pad = 1;      // left to k_row_stats_radix
+        // place is that of its key, a range beyond FP32, one value only) has no
+        // interval here.
+        if (!(hi - lo < INFINITY) || (hi == lo && m > many_keys(n))) {
+            if (tid == 0) out[k].pad = 1;      // left to k_row_stats_crowded
             __syncthreads();
             continue;
         }
@@ -330,86 +456,23 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
             const int b = (int)((x - lo) * inv);
             return b < 0 ? 0 : b > kBins - 1 ? kBins - 1 : b;
         };
-        each([&](float x) { atomicAdd(&bs.hist[bin_of(x)], 1u); });
+        Counter<E == 0> count{bs.hist};
+        each([&](float x) { count.add(bin_of(x)); });
+        count.flush();
         __syncthreads();
-        // the intervals that hold the ranks
-        {
-            const uint4 h = *reinterpret_cast<const uint4 *>(&bs.hist[4 * tid]);
-            const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
-            uint32_t inc = tot;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t o = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += o;
-            }
-            if (lane == 63) bs.wtot[wave] = inc;
-            __syncthreads();
-            uint32_t before = inc - tot;
-            for (int w = 0; w < wave; ++w) before += bs.wtot[w];
-#pragma unroll
-            for (int q = 0; q < NTGT; ++q) {
-                const uint32_t r = (uint32_t)__builtin_amdgcn_readlane(want, q);
-                if (r >= before && r < before + tot) {
-                    uint32_t acc = before;
-                    int d = 0;
-                    while (d < 3 && r >= acc + c[d]) acc += c[d++];
-                    bs.bin[q] = 4 * tid + d;
-                    bs.rank[q] = (int32_t)(r - acc);
-                    bs.cnt[q] = (int32_t)c[d];
-                }
-            }
-        }
-        __syncthreads();
-        // one list per interval: lane q has rank q; equal intervals share the
-        // first one's list
-        if (wave == 0) {
-            const int b = lane < NTGT ? bs.bin[lane] : -1 - lane;
-            const int c = lane < NTGT ? bs.cnt[lane] : 0;
-            int first = lane;
-#pragma unroll
-            for (int q = NTGT - 1; q >= 0; --q)
-                if (__builtin_amdgcn_readlane(b, q) == b && q < first) first = q;
-            const bool own = lane < NTGT && first == lane;
-            int at = 0, total = 0;
-#pragma unroll
-            for (int q = 0; q < NTGT; ++q) {
-                const int cq = __builtin_amdgcn_readlane(own ? c : 0, q);
-                if (q < first) at += cq;
-                total += cq;
-            }
-            if (lane < NTGT) bs.off[lane] = at;
-            if (own) {
-                bs.mark[b] = (uint8_t)(1 + lane);
-                bs.cursor[lane] = at;
-            }
-            if (lane == 0) bs.total = total;
-        }
-        __syncthreads();
-        const bool crowded = bs.total > kCand;
+        find_intervals(bs, want);
+        const bool crowded = bs.total > kCand || bs.most > many_keys(n);
         if (!crowded) {
             each([&](float x) {
                 const int q = bs.mark[bin_of(x)];
                 if (q) bs.cand[atomicAdd(&bs.cursor[q - 1], 1)] = fkey(x);
             });
             __syncthreads();
-            for (int q = wave; q < NTGT; q += NW) {
-                const uint32_t *l = bs.cand + bs.off[q];
-                const int c = bs.cnt[q], r = bs.rank[q];
-                for (int e = lane; e < c; e += 64) {
-                    const uint32_t x = l[e];
-                    int less = 0, same = 0;
-#pragma unroll 4
-                    for (int i = 0; i < c; ++i) {
-                        less += l[i] < x;
-                        same += l[i] == x;
-                    }
-                    if (r >= less && r < less + same) bs.key[q] = x;   // (equal keys write the same)
-                }
-            }
+            rank_lists(bs, want);
         }
         __syncthreads();
         if (crowded) {
-            if (tid == 0) out[k].pad = 1;      // left to k_row_stats_radix
+            if (tid == 0) out[k].pad = 1;
             continue;
         }
         row_tail<ST_T>(each, bs.key, row[k], m, wsum, wcnt, out + k);
@@ -417,22 +480,180 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
     }
 }
 
-// The rows that k_row_stats left, by radix select.
-__global__ __launch_bounds__(SEL_T) void k_row_stats_radix(const float *S, int64_t ld, int32_t n, RowStats *out) {
-    __shared__ SelShared sm;
-    __shared__ double wsum[SEL_T / 64];
-    __shared__ int32_t wcnt[SEL_T / 64];
-    const int tid = threadIdx.x;
+// The rows that k_row_stats left.  Here the cut is of the keys, so that the
+// width of an interval follows the exponent (a far outlier costs a tenth of
+// the intervals, not all but one), and it is repeated: the interval of a rank
+// that holds too many keys is cut again, between the least and the largest of
+// them, until few keys are left or one key only (ties).  A cut divides a
+// range of keys by at least 128 (2048 intervals over at most eleven lists),
+// so five serve any row; most take one or two.  1000 points of which one lies
+// far out: 42 us for all rows, 1718 by counting one long list, 76 with the
+// digits of a radix select; 5000: 412 us, 520 with the digits.
+template <int E>
+__global__ __launch_bounds__(ST_T) void k_row_stats_crowded(const float *S, int64_t ld, int32_t n, RowStats *out) {
+    __shared__ BinShared bs;
+    __shared__ double wsum[ST_T / 64];
+    __shared__ int32_t wcnt[ST_T / 64];
+    __shared__ uint32_t la[NTGT], lb[NTGT];   // the lists of the cut: least and largest key, ascending
+    __shared__ int32_t lsh[NTGT];             // ... keys to an interval (a power of two: its exponent)
+    __shared__ uint32_t kmin[NTGT], kmax[NTGT];
+    __shared__ int32_t nlists, lbits, wanted[NTGT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m = n - 1;
-    for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
-        if (out[k].pad == 0) continue;
+    unsigned long long left = 0ull;           // of 64 rows of this workgroup, those still to do
+    for (int64_t base = blockIdx.x, k;;) {
+        if (left == 0ull) {
+            if (base >= n) break;
+            const int64_t mine = base + (int64_t)lane * gridDim.x;
+            left = __ballot(mine < n && out[mine < n ? mine : 0].pad != 0);
+            base += 64 * (int64_t)gridDim.x;
+            __syncthreads();                  // (row_tail rewrites pad)
+            continue;
+        }
+        k = base + ((int64_t)__builtin_ctzll(left) - 64) * gridDim.x;
+        left &= left - 1ull;
         const float *row = S + k * ld;
-        if (tid < NTGT) sm.rank[tid] = stat_rank(tid, m);
-        radix_select(sm, m, NTGT, [&](int64_t j) { return fkey(row[j < k ? j : j + 1]); });
-        row_tail<SEL_T>([&](auto f) {
-            for (int64_t j = tid; j < n; j += SEL_T)
-                if (j != k) f(row[j]);
-        }, sm.pref, row[k], m, wsum, wcnt, out + k);
+        float v[E > 0 ? E : 1];
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int j = tid + e * ST_T;
+                v[e] = j < n ? row[j] : 0.0f;
+            }
+        }
+        auto each = [&](auto f) {
+            if constexpr (E > 0) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int j = tid + e * ST_T;
+                    if (j < n && j != (int)k) f(v[e]);
+                }
+            } else {
+                // eight loads in flight
+                for (int j0 = tid; j0 < n; j0 += 8 * ST_T) {
+                    float x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = j0 + u * ST_T < n ? row[j0 + u * ST_T] : 0.0f;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int j = j0 + u * ST_T;
+                        if (j < n && j != (int)k) f(x[u]);
+                    }
+                }
+            }
+        };
+        // the first list: every key
+        if (tid == 0) {
+            kmin[0] = 0xffffffffu;
+            kmax[0] = 0u;
+        }
+        if (tid < NTGT) {
+            wanted[tid] = bs.rank[tid] = stat_rank(tid, m);
+            bs.bin[tid] = 0;
+            bs.cnt[tid] = (int32_t)m;
+        }
+        __syncthreads();
+        uint32_t a = 0xffffffffu, b = 0u;
+        each([&](float x) {
+            a = min(a, fkey(x));
+            b = max(b, fkey(x));
+        });
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            a = min(a, (uint32_t)__shfl_xor((int)a, off, 64));
+            b = max(b, (uint32_t)__shfl_xor((int)b, off, 64));
+        }
+        if (lane == 0) {
+            atomicMin(&kmin[0], a);
+            atomicMax(&kmax[0], b);
+        }
+        __syncthreads();
+        bool done = false;
+        while (!done) {
+            // Lane q has rank q, in the list of the first rank that shares its
+            // interval, whose bounds are kmin and kmax: a list of one key has
+            // the answer, the others are cut again.
+            if (wave == 0) {
+                const bool live = lane < NTGT && wanted[lane < NTGT ? lane : 0] >= 0;
+                const int b0 = live ? bs.bin[lane] : -1 - lane;
+                int own = lane;
+#pragma unroll
+                for (int q = NTGT - 1; q >= 0; --q)
+                    if (__builtin_amdgcn_readlane(b0, q) == b0 && q < own) own = q;
+                const uint32_t x = live ? kmin[own] : 0u, y = live ? kmax[own] : 0u;
+                const bool cut = live && x != y, mine = cut && own == lane;
+                if (live && !cut) bs.key[lane] = x;
+                // lists in ascending order of their keys; keys before this rank's list
+                int at = 0, before = 0, lists = 0;
+#pragma unroll
+                for (int q = 0; q < NTGT; ++q) {
+                    const int bq = __builtin_amdgcn_readlane(b0, q);
+                    const int cq = __builtin_amdgcn_readlane(mine ? bs.cnt[lane] : 0, q);
+                    if (cq > 0) {
+                        ++lists;
+                        if (bq < b0) {
+                            ++at;
+                            before += cq;
+                        }
+                    }
+                }
+                const int bits = lists > 8 ? 7 : lists > 4 ? 8 : lists > 2 ? 9 : lists > 1 ? 10 : 11;
+                if (mine) {
+                    const int span = 32 - __builtin_clz(y - x);
+                    la[at] = x;
+                    lb[at] = y;
+                    lsh[at] = span > bits ? span - bits : 0;
+                }
+                if (lane < NTGT) wanted[lane] = cut ? before + bs.rank[lane] : -1;
+                if (lane == 0) {
+                    nlists = lists;
+                    lbits = bits;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bs.hist[tid + q * ST_T] = 0u;
+            reinterpret_cast<uint32_t *>(bs.mark)[tid] = 0u;
+            __syncthreads();
+            const int lists = nlists, bits = lbits;
+            if (lists == 0) break;
+            const int32_t want = lane < NTGT ? wanted[lane] : -1;
+            auto slot = [&](uint32_t key) -> int {      // interval of a key, -1: in no list
+                int d = 0;
+                for (int u = 1; u < lists; ++u) d += key >= la[u];
+                return key >= la[d] && key <= lb[d] ? (int)(d << bits | (key - la[d]) >> lsh[d]) : -1;
+            };
+            Counter<E == 0> count{bs.hist};
+            each([&](float x) {
+                const int b1 = slot(fkey(x));
+                if (b1 >= 0) count.add(b1);
+            });
+            count.flush();
+            __syncthreads();
+            find_intervals(bs, want);
+            done = bs.total <= kCand && bs.most <= many_keys(n);
+            if (tid < NTGT) {
+                kmin[tid] = 0xffffffffu;
+                kmax[tid] = 0u;
+            }
+            __syncthreads();
+            each([&](float x) {
+                const uint32_t key = fkey(x);
+                const int b1 = slot(key);
+                const int q = b1 >= 0 ? bs.mark[b1] : 0;
+                if (q == 0) return;
+                if (done) {
+                    bs.cand[atomicAdd(&bs.cursor[q - 1], 1)] = key;
+                } else {
+                    // (the bounds only ever widen: most keys change neither)
+                    if (key < __atomic_load_n(&kmin[q - 1], __ATOMIC_RELAXED)) atomicMin(&kmin[q - 1], key);
+                    if (key > __atomic_load_n(&kmax[q - 1], __ATOMIC_RELAXED)) atomicMax(&kmax[q - 1], key);
+                }
+            });
+            __syncthreads();
+            if (done) rank_lists(bs, want);
+        }
+        __syncthreads();
+        row_tail<ST_T>(each, bs.key, row[k], m, wsum, wcnt, out + k);
         __syncthreads();
     }
 }
@@ -1047,12 +1268,17 @@ apx_status run_features(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, Row
                         float *F, float *sigma) {
     hipStream_t s = ctx->stream;
     const unsigned rows = grid_rows(n, ctx->num_cus * 4);     // four workgroups fit a compute unit
-    if (n <= 2 * ST_T) k_row_stats<2><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
-    else if (n <= 4 * ST_T) k_row_stats<4><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
-    else if (n <= 8 * ST_T) k_row_stats<8><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
-    else if (n <= 16 * ST_T) k_row_stats<16><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
-    else k_row_stats<0><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
-    k_row_stats_radix<<<grid_rows(n, ctx->num_cus), SEL_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    auto both = [&](auto held) {
+        constexpr int E = decltype(held)::value;
+        k_row_stats<E><<<rows, ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+        // (mostly nothing is left to do: no more workgroups than its registers let run)
+        k_row_stats_crowded<E><<<grid_rows(n, ctx->num_cus), ST_T, 0, s>>>(S, ld, (int32_t)n, stats);
+    };
+    if (n <= 2 * ST_T) both(std::integral_constant<int, 2>{});
+    else if (n <= 4 * ST_T) both(std::integral_constant<int, 4>{});
+    else if (n <= 8 * ST_T) both(std::integral_constant<int, 8>{});
+    else if (n <= 16 * ST_T) both(std::integral_constant<int, 16>{});
+    else both(std::integral_constant<int, 0>{});
     HIP_TRY(hipGetLastError(), "row statistics");
     k_sigma<<<1, SEL_T, 0, s>>>(stats, (int32_t)n, sigma);
     HIP_TRY(hipGetLastError(), "sigma");
