@@ -744,7 +744,11 @@ constexpr int TP = 32;              // points per tile
 constexpr int LW1 = NF + 4;         // padded row of W1^T in LDS (bf16)
 constexpr int LW2 = NH + 4;         // padded row of W2^T and of the activations
 constexpr int LDZ = NH + 1;         // padded row of a pre-activation gradient
-constexpr int kMaxTileBlocks = 256; // workgroups of the gradient kernel (= partial gradients)
+constexpr int kMaxTileBlocks = 256; // workgroups of the gradient kernel
+// Partial gradients are FP32 sums over at most 64 points and are added in
+// FP64: a slot is one tile or two, whichever gives the busiest workgroup fewer
+// tiles (two on a tie: half the partials).  At most kMaxSlots of them (154 MB) are held at a time.
+constexpr int64_t kMaxSlots = 2048;
 
 struct TileShared {
     uint16_t w1t[NH * LW1];         // W1^T [unit][feature]
@@ -897,37 +901,44 @@ struct BwdArgs {
     const float *F, *T, *w;         // features (count x 16), targets (count x 2), weights (count)
     const int64_t *rows;            // nullable batch indices into F, T, w
     int64_t count;
-    float *gpart;                   // [gridDim.x][NPARAM]
-    double *lpart;                  // [gridDim.x]
+    int64_t slot0;                  // first slot of this launch
+    int32_t slots, per;             // slots of this launch, tiles of a slot
+    float *gpart;                   // [slots][NPARAM]
+    double *lpart;                  // [slots]
 };
 
 // Forward and backward of the workgroup's tiles in one kernel (activations
 // and slopes never leave the chip); the products of the backward pass run on
 // the FP32 matrix op (32x32x2: bf16 activations and weights are exact in
-// FP32, gradients stay FP32).  Writes the workgroup's partial gradient.  8192
-// rows: 36 us (forward 52 and backward 149 us while the activations went
+// FP32, gradients stay FP32).  Writes a partial gradient per slot.  8192
+// rows: 37 us (forward 52 and backward 149 us while the activations went
 // through memory and the products ran on the vector units).
+// ONE: a workgroup has one tile.
+template <bool ONE>
 __global__ __launch_bounds__(TW) void k_mlp_bwd(BwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     BwdShared &sh = *reinterpret_cast<BwdShared *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, hi = lane >> 5;
-    float *g = a.gpart + (int64_t)blockIdx.x * NPARAM;
     v4s xa[2];
-    tile_features(a.F, a.rows, a.count, (int64_t)blockIdx.x * TP, lane, xa);   // in flight with the weights
+    const int64_t first = (a.slot0 + blockIdx.x) * a.per;
+    tile_features(a.F, a.rows, a.count, first * TP, lane, xa);   // in flight with the weights
     tile_weights(sh.t, a.theta);
     __syncthreads();
 
+    const int64_t tiles = (a.count + TP - 1) / TP;
+    for (int slot = blockIdx.x; slot < a.slots; slot += ONE ? a.slots : gridDim.x) {
+    float *g = a.gpart + (int64_t)slot * NPARAM;
     v16f dw2[4], dw1 = zero16();    // dW2 rows 32 wave + ., dW1^T-tile: features x units 32 wave + .
 #pragma unroll
     for (int q = 0; q < 4; ++q) dw2[q] = zero16();
     float dw3 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f;
     double lsum = 0.0;
 
-    const int64_t tiles = (a.count + TP - 1) / TP;
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t tile0 = (a.slot0 + slot) * a.per;
+    for (int64_t tile = tile0; tile < tile0 + (ONE ? 1 : a.per) && tile < tiles; ++tile) {
         const int64_t p0 = tile * TP;
-        if (tile != blockIdx.x) tile_features(a.F, a.rows, a.count, p0, lane, xa);
+        if (!ONE && tile != first) tile_features(a.F, a.rows, a.count, p0, lane, xa);
         if (wave == 3) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -1031,15 +1042,19 @@ __global__ __launch_bounds__(TW) void k_mlp_bwd(BwdArgs a) {
     if (wave == 0) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
-        if (lane == 0) a.lpart[blockIdx.x] = lsum;
+        if (lane == 0) a.lpart[slot] = lsum;
+    }
     }
 }
 
-// grad[e] = sum over workgroups of the partials (FP64): 64 entries x 16
+// grad[e] = sum over the slots of the partials (FP64): 64 entries x 16
 // slices of the partials per workgroup, slices added in order.  256 partials:
-// 6 us (38 us for 128 with one serial sum per entry).
+// 6 us (38 us for 128 with one serial sum per entry).  Where the slots come in
+// several launches, acc (NPARAM + 1 doubles, the loss last) carries the sums:
+// nullable, read unless first; grad and loss are written at the last.
 __global__ __launch_bounds__(1024) void k_mlp_reduce(const float *gpart, const double *lpart, int32_t nblk,
-                                                     float *grad, double *loss) {
+                                                     float *grad, double *loss, double *acc, int first,
+                                                     int last) {
     __shared__ double part[16][64];
     const int ex = threadIdx.x & 63, sl = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + ex;
@@ -1061,14 +1076,20 @@ __global__ __launch_bounds__(1024) void k_mlp_reduce(const float *gpart, const d
         double tot = 0.0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) tot += part[q][ex];
-        grad[e] = (float)tot;
+        if (!first) tot += acc[e];
+        if (last) grad[e] = (float)tot;
+        else acc[e] = tot;
     }
     if (loss && blockIdx.x == 0 && sl == 1) {
         double t = 0.0;
         for (int b = ex; b < nblk; b += 64) t += lpart[b];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
-        if (ex == 0) *loss = t;
+        if (ex == 0) {
+            if (!first) t += acc[NPARAM];
+            if (last) *loss = t;
+            else acc[NPARAM] = t;
+        }
     }
 }
 
@@ -1298,16 +1319,21 @@ apx_status run_forward(apx_ctx *ctx, const FwdArgs &fa) {
 
 
 struct BwdLayout {
-    size_t o_gp, o_lp, bytes;
-    int64_t nblk;
+    size_t o_gp, o_lp, o_acc, bytes;
+    int64_t slots, held;     // partial gradients, of which so many in a launch
+    int32_t per;             // tiles of one
 };
 BwdLayout bwd_layout(int64_t count) {
     const int64_t tiles = (count + TP - 1) / TP;
     WsLayout W;
     BwdLayout o{};
-    o.nblk = tiles < kMaxTileBlocks ? tiles : kMaxTileBlocks;
-    o.o_gp = W.take(sizeof(float) * NPARAM * (size_t)o.nblk);
-    o.o_lp = W.take(sizeof(double) * (size_t)o.nblk);
+    const int64_t wg = kMaxTileBlocks, ones = (tiles + wg - 1) / wg, pairs = ((tiles + 1) / 2 + wg - 1) / wg;
+    o.per = ones < 2 * pairs ? 1 : 2;
+    o.slots = (tiles + o.per - 1) / o.per;
+    o.held = o.slots < kMaxSlots ? o.slots : kMaxSlots;
+    o.o_gp = W.take(sizeof(float) * NPARAM * (size_t)o.held);
+    o.o_lp = W.take(sizeof(double) * (size_t)o.held);
+    o.o_acc = W.take(o.slots > o.held ? sizeof(double) * (NPARAM + 1) : 0);
     o.bytes = W.off;
     return o;
 }
@@ -1389,12 +1415,19 @@ apx_status apx_mlp_backward(apx_ctx *ctx, const float *theta, const float *F, co
     ba.gpart = reinterpret_cast<float *>(b + BL.o_gp);
     ba.lpart = reinterpret_cast<double *>(b + BL.o_lp);
     const size_t lds = sizeof(BwdShared);
-    HIP_TRY(hipFuncSetAttribute((const void *)k_mlp_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds), "lds");
-    k_mlp_bwd<<<(unsigned)BL.nblk, TW, lds, ctx->stream>>>(ba);
-    HIP_TRY(hipGetLastError(), "network backward");
-    k_mlp_reduce<<<(NPARAM + 63) / 64, 1024, 0, ctx->stream>>>(ba.gpart, ba.lpart, (int32_t)BL.nblk, grad, loss);
-    HIP_TRY(hipGetLastError(), "gradient reduce");
+    const auto kern = BL.per == 1 && BL.slots <= kMaxTileBlocks ? k_mlp_bwd<true> : k_mlp_bwd<false>;
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds), "lds");
+    ba.per = BL.per;
+    for (ba.slot0 = 0; ba.slot0 < BL.slots; ba.slot0 += BL.held) {
+        const int64_t left = BL.slots - ba.slot0;
+        ba.slots = (int32_t)(left < BL.held ? left : BL.held);
+        kern<<<ba.slots < kMaxTileBlocks ? ba.slots : kMaxTileBlocks, TW, lds, ctx->stream>>>(ba);
+        HIP_TRY(hipGetLastError(), "network backward");
+        k_mlp_reduce<<<(NPARAM + 63) / 64, 1024, 0, ctx->stream>>>(ba.gpart, ba.lpart, ba.slots, grad, loss,
+                                                                   reinterpret_cast<double *>(b + BL.o_acc),
+                                                                   ba.slot0 == 0, left <= BL.held);
+        HIP_TRY(hipGetLastError(), "gradient reduce");
+    }
     return APX_OK;
 }
 

@@ -47,3 +47,18 @@ def test_forward_tiles(count):
     err = np.abs(y - ref)
     assert np.all(err <= 2.0 ** -6 * scale)
     assert np.mean(err <= 1e-4 * scale) >= (0.99 if count > 100 else 0.9)
+
+
+@pytest.mark.parametrize("count", [8192, 8224, 65536, 131072, 131136, 400000])
+def test_partial_sums_stay_short(count):
+    """The gradient of `count` copies of one row against `count` times that
+    row's: equal addends, so FP32 sums over L of them differ from the product
+    by at most (L + 1) 2^-24 of it.  L is at most 64 whatever the batch (the
+    partials are added in FP64), plus one rounding of the result."""
+    theta = t32(synth.mlp_params(5))
+    X, T, w = (t32(a) for a in synth.mlp_batch(4, 5))
+    one, l1 = apx.apx_mlp_backward(theta, X, T, w, rows=torch.full((1,), 2, device="cuda"))
+    g, loss = apx.apx_mlp_backward(theta, X, T, w, rows=torch.full((count,), 2, device="cuda"))
+    ref = one.double() * count
+    assert bool(((g.double() - ref).abs() <= 66 * 2.0 ** -24 * ref.abs()).all())
+    assert abs(loss.item() - count * l1.item()) <= 1e-12 * count * l1.item()
