@@ -394,6 +394,7 @@ struct BatchSpec {
 size_t batched_ws_bytes(int32_t count, const BatchSpec *spec, int num_cus);
 // Workspace bytes of the other calls (apx_workspace_size).
 size_t similarity_ws_bytes(int64_t n);
+size_t similarity_ws_least(int64_t n);     // without room for the median's window
 // Matrix-free S (similarity.hip): rows of S rebuilt from X one panel at a
 // time, each entry with the value ap_similarity stores.
 struct MfSim {

@@ -256,7 +256,7 @@ namespace {
 // Workspace of lap_solve: [landmark tables, X_M, S_M, R_M, A_M, exemplars,
 // flags, distances] then the slice of the landmark similarity and solve.
 struct LapLayout {
-    size_t o_lm, o_xm, o_S, o_R, o_A, o_lab, o_ex, o_m, o_EX, o_flag, o_dist, o_sum, head, tail;
+    size_t o_lm, o_xm, o_S, o_R, o_A, o_lab, o_ex, o_m, o_EX, o_flag, o_dist, o_sum, head, tail, least;
 };
 LapLayout lap_layout(int64_t n, int64_t d, int64_t L, int num_cus) {
     const int64_t ldL = round64(L), ldm = d;
@@ -276,7 +276,9 @@ LapLayout lap_layout(int64_t n, int64_t d, int64_t L, int num_cus) {
     o.o_sum = W.take(sizeof(double) * 2);
     o.head = W.off;
     const size_t sim = similarity_ws_bytes(L), sol = solve_ws_bytes(L, ldL, num_cus);
+    const size_t few = similarity_ws_least(L);
     o.tail = sim > sol ? sim : sol;
+    o.least = few > sol ? few : sol;       // the landmarks' median without its window
     return o;
 }
 
@@ -361,6 +363,7 @@ extern "C" apx_status lap_solve(apx_ctx *ctx, const float *X, int64_t n, int64_t
                  o_sum = LL.o_sum, head = LL.head;
     ctx->ws_base = 0;
     apx_status st = ws_reserve(ctx, head + LL.tail);
+    if (st == APX_ENOMEM) st = ws_reserve(ctx, head + LL.least);
     if (st != APX_OK) return st;
     char *b = static_cast<char *>(ctx->ws);
     int64_t *dlm = reinterpret_cast<int64_t *>(b + o_lm);
@@ -927,6 +930,10 @@ extern "C" apx_status lap_full_solve(apx_ctx *ctx, const float *X, int64_t n, in
     const size_t sim = similarity_ws_bytes(F.amax), sol = solve_ws_bytes(F.amax, F.lda, ctx->num_cus);
     ctx->ws_base = 0;
     apx_status st = ws_reserve(ctx, F.head + (sim > sol ? sim : sol));
+    if (st == APX_ENOMEM) {
+        const size_t few = similarity_ws_least(F.amax);
+        st = ws_reserve(ctx, F.head + (few > sol ? few : sol));
+    }
     if (st != APX_OK) return st;
     lapf_carve(F, static_cast<char *>(ctx->ws));
     // every point takes part in the assignments: non-finite X is rejected first

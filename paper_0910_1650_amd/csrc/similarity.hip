@@ -1143,6 +1143,7 @@ SimLayout sim_layout(int64_t n) {
 }  // namespace
 
 size_t apx::similarity_ws_bytes(int64_t n) { return sim_layout(n).bytes; }
+size_t apx::similarity_ws_least(int64_t n) { return sim_layout(n).base; }
 
 extern "C" apx_status ap_similarity(apx_ctx *ctx, const float *X, int64_t n, int64_t d, int64_t ldx,
                                     float *S, int64_t ld, int32_t pref_mode, const float *pref_vec,
@@ -1168,10 +1169,14 @@ extern "C" apx_status ap_similarity(apx_ctx *ctx, const float *X, int64_t n, int
 
     const SimLayout SL = sim_layout(n);
     const size_t o_n = SL.o_n, o_mm = SL.o_mm, o_sel = SL.o_sel, o_h = SL.o_h, o_r = SL.o_r;
-    // The median's window needs room for the keys set aside; a caller's
-    // workspace without it gets the radix select.
+    // The median's window needs room for the keys set aside (1.7% of S); where
+    // there is none (a caller's workspace without it, a device without that
+    // much memory left) the radix select runs.  The workspace does not grow
+    // for it while a caller inside the library keeps data below ws_base.
     const bool median = pref_mode == APX_PREF_MEDIAN;
-    const bool windowed = median && (!ctx->ws_external || ctx->ws_base + SL.bytes <= ctx->ws_bytes);
+    bool windowed = median;
+    if (windowed && ctx->ws_base + SL.bytes > ctx->ws_bytes)
+        windowed = !ctx->ws_external && ctx->ws_base == 0 && ws_reserve(ctx, SL.bytes) == APX_OK;
     apx_status st = ws_reserve(ctx, ctx->ws_base + (windowed ? SL.bytes : SL.base));
     if (st != APX_OK) return st;
 
