@@ -86,18 +86,39 @@ constexpr int kSampleTail = 512;   // ... the window spans the sample's median r
 // Up to here every key is set aside and the window is the range of S (no
 // sample: 300 points 78 us instead of 91).
 constexpr int64_t kWholeN = 512;
+// Samples an interval that holds an end of the window may have (0.4% of them
+// on either side: the lists hold twice what the window makes expected).
+constexpr uint32_t kEdgeMany = 256;
+constexpr uint32_t kNoBin = 0xffffffffu;   // SelWin::bin of a rank whose key is known
+// Keys up to which the last workgroup of the ranking cuts crowded intervals
+// again by itself (300 points of two clusters: 132 us, 162 with the select over
+// S).  Above, the host starts another count and ranking of the lists (20000
+// points of two far clusters, whose median lies at an edge of the gap: 2.36 ms
+// with the noise, 3.35 with the select).
+constexpr uint32_t kRecut = 1u << 18;
+constexpr int32_t kCutAgain = 2;
+// How k_win_count and k_win_rank cut the keys set aside: the sample's window,
+// the bounds of S, or the crowded interval of a cut before.
+enum { CUT_WINDOW, CUT_WHOLE, CUT_AGAIN };
 
 struct SelSeg {                    // one 128-byte line per list
     uint32_t count, pad;
     unsigned long long below;      // keys below the window
-    uint32_t fill[28];
+    unsigned long long at[2];      // ties: keys equal to its lower and its upper end
+    uint32_t fill[24];
 };
 struct SelWin {
     float vlo, vhi;                // the window, both inclusive; neither is a zero, so values
                                    // compare as their keys do
-    uint32_t lo;                   // key of vlo
+    uint32_t lo;                   // key of vlo (a repeated cut: least key of the interval cut again)
     uint32_t shift;                // interval of a key: (key - lo) >> shift < kWinBins
-    int32_t miss;                  // the median was not found this way
+    uint32_t hi;                   // repeated cut: largest key of the interval
+    int32_t miss;                  // 1: the median was not found this way; kCutAgain: its interval is too
+                                   // crowded to be ranked
+    // Similarities crowd near an end, which is then a value that many entries
+    // may share: entries equal to an end are counted, not set aside (an end may
+    // be +0 here; S holds no -0: the Gram sum starts from +0 and x - x is +0).
+    int32_t ties;
     uint32_t bin[2];               // intervals of the two ranks ...
     uint32_t rank[2];              // ... and the ranks inside them
     uint32_t kmin[2], kmax[2];     // bounds of the keys in the two intervals
@@ -227,13 +248,15 @@ __global__ __launch_bounds__(NT, 3) void k_sim_gemm(SimArgs a) {
         nc[e] = col0 + e < a.n ? a.nrm[col0 + e] : 0.0f;
     }
     float wlo = 0.0f, whi = 0.0f;
-    uint32_t below = 0u;
+    int wties = 0;
+    uint32_t below = 0u, at_lo = 0u, at_hi = 0u;
     int nheld = 0;
     SelSeg *const seg = COUNT ? a.segs + blockIdx.x % kSegs : nullptr;
     uint32_t *const list = COUNT ? a.cand + (int64_t)(blockIdx.x % kSegs) * a.cap : nullptr;
     if constexpr (COUNT) {
         wlo = a.win->vlo;
         whi = a.win->vhi;
+        wties = a.win->ties;
     }
     auto append = [&]() {
         uint32_t at = 0u;
@@ -308,7 +331,10 @@ __global__ __launch_bounds__(NT, 3) void k_sim_gemm(SimArgs a) {
     // that all lanes take part; tiles above the diagonal and inside S need no
     // test of the indices.
     if constexpr (COUNT) {
-        auto walk = [&](auto every) {
+        // with ties: entries equal to an end are counted apart (both ends one
+        // value: in at_lo; no value lies between then)
+        const float one = wlo == whi ? __builtin_nanf("") : whi;
+        auto walk = [&](auto every, auto ties) {
 #pragma unroll
             for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -325,7 +351,14 @@ __global__ __launch_bounds__(NT, 3) void k_sim_gemm(SimArgs a) {
                             if constexpr (!decltype(every)::value)
                                 up = col0 + c < a.n && row0 + mb + q < a.n && (!diag_tile || mb + q < c);
                             below += __popcll(__ballot(up && v < wlo));
-                            const unsigned long long m = __ballot(up && v >= wlo && v <= whi);
+                            unsigned long long m;
+                            if constexpr (decltype(ties)::value) {
+                                at_lo += __popcll(__ballot(up && v == wlo));
+                                at_hi += __popcll(__ballot(up && v == one));
+                                m = __ballot(up && v > wlo && v < one);
+                            } else {
+                                m = __ballot(up && v >= wlo && v <= whi);
+                            }
                             if (m == 0ull) continue;
                             if ((m >> lane) & 1ull) held[wave][nheld + __popcll(m & ((1ull << lane) - 1ull))] = fkey(v);
                             nheld += __popcll(m);
@@ -334,8 +367,15 @@ __global__ __launch_bounds__(NT, 3) void k_sim_gemm(SimArgs a) {
                     }
                 }
         };
-        if (!diag_tile && row0 + BM <= a.n && col0 + BM <= a.n) walk(std::true_type{});
-        else walk(std::false_type{});
+        if (wties) {
+            walk(std::false_type{}, std::true_type{});
+            if (lane == 0 && at_lo) atomicAdd(&seg->at[0], (unsigned long long)at_lo);
+            if (lane == 0 && at_hi) atomicAdd(&seg->at[1], (unsigned long long)at_hi);
+        } else if (!diag_tile && row0 + BM <= a.n && col0 + BM <= a.n) {
+            walk(std::true_type{}, std::false_type{});
+        } else {
+            walk(std::false_type{}, std::false_type{});
+        }
         if (nheld) append();
         if (lane == 0 && below) atomicAdd(&seg->below, (unsigned long long)below);
     }
@@ -580,11 +620,40 @@ __device__ __forceinline__ void st_dev(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The keys of ranks r0 and r1 (ascending) among the workgroup's, which lie
+// between least and most (others: 0xffffffff, above both ranks), bit by bit
+// from the highest in which they differ: count the keys below.  under: a pair
+// of zeros for each bit.
+template <int N>
+__device__ __forceinline__ void two_ranks(const uint32_t (&key)[N], int r0, int r1, uint32_t least, uint32_t most,
+                                          uint32_t (*under)[2], uint32_t &e0, uint32_t &e1) {
+    const int bits = least == most ? 0 : 32 - __builtin_clz(least ^ most);
+    e0 = e1 = bits < 32 ? least >> bits << bits : 0u;
+    for (int bit = bits - 1; bit >= 0; --bit) {
+        const uint32_t t0 = e0 | 1u << bit, t1 = e1 | 1u << bit;
+        uint32_t n0 = 0u, n1 = 0u;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            n0 += __popcll(__ballot(key[e] < t0));
+            n1 += __popcll(__ballot(key[e] < t1));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicAdd(&under[bit][0], n0);
+            atomicAdd(&under[bit][1], n1);
+        }
+        __syncthreads();
+        if (r0 >= (int)under[bit][0]) e0 = t0;
+        if (r1 >= (int)under[bit][1]) e1 = t1;
+    }
+}
+
 // Similarities of kSamples pseudo-random pairs (16 lanes to a pair), then, in
 // the last workgroup, the window: the values of the sample's ranks at kSampleTail
 // either side of the middle, widened to the intervals (of kWinBins over the
-// sample's range) that hold them.  The window only has to hold the median;
-// nothing else depends on it.
+// sample's range) that hold them.  Where an interval has many samples (a far
+// point or cluster stretches the range, ties) the ends are values of samples
+// at those ranks.  The window only has to hold the median; nothing
+// else depends on it.
 constexpr int SMP_T = 1024, SMP_BLOCKS = 128;
 __global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n, int64_t d, int64_t ldx,
                                                       const float *nrm, uint32_t *smp, SelWin *win,
@@ -594,6 +663,7 @@ __global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n,
     __shared__ float red[2][SMP_T / 64];
     __shared__ uint32_t wtot[SMP_T / 64];
     __shared__ int edge[2];
+    __shared__ uint32_t held[4], under[2][32][2];   // samples in the ends' intervals; below a key, by its bit
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // four pairs at a time per 16 lanes
     constexpr int PER = kSamples / SMP_BLOCKS / (SMP_T / 16);
@@ -653,40 +723,101 @@ __global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n,
         hi = fmaxf(hi, red[1][w]);
     }
     const float inv = (float)(kWinBins - 1) / (hi - lo);
+    auto bin_of = [&](float x) {
+        const int b = (int)((x - lo) * inv);
+        return b < 0 ? 0 : b > kWinBins - 1 ? kWinBins - 1 : b;
+    };
+    // (an eighth first: where a quarter of it lies in one interval, the others
+    // would only wait for that counter)
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int b = (int)((v[e] - lo) * inv);
-        atomicAdd(&hist[b < 0 ? 0 : b > kWinBins - 1 ? kWinBins - 1 : b], 1u);
-    }
+    for (int e = 0; e < E / 8; ++e) atomicAdd(&hist[bin_of(v[e])], 1u);
+    if (tid < 128) (&under[0][0][0])[tid] = 0u;
     __syncthreads();
-    const uint4 h = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
-    const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
-    uint32_t inc = tot;
+    bool crowded = __syncthreads_or(hist[bin_of(v[0])] > kSamples / 8 / 4);
+    if (!crowded) {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += o;
-    }
-    if (lane == 63) wtot[wave] = inc;
-    __syncthreads();
-    uint32_t before = inc - tot;
-    for (int w = 0; w < wave; ++w) before += wtot[w];
+        for (int e = E / 8; e < E; ++e) atomicAdd(&hist[bin_of(v[e])], 1u);
+        __syncthreads();
+        const uint4 h = *reinterpret_cast<const uint4 *>(&hist[4 * tid]);
+        const uint32_t c[4] = {h.x, h.y, h.z, h.w}, tot = h.x + h.y + h.z + h.w;
+        uint32_t inc = tot;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const uint32_t r = kSamples / 2 + (q ? kSampleTail : -kSampleTail);
-        if (r >= before && r < before + tot) {
-            uint32_t acc = before;
-            int e = 0;
-            while (e < 3 && r >= acc + c[e]) acc += c[e++];
-            edge[q] = 4 * tid + e;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += o;
         }
+        if (lane == 63) wtot[wave] = inc;
+        __syncthreads();
+        uint32_t before = inc - tot;
+        for (int w = 0; w < wave; ++w) before += wtot[w];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t r = kSamples / 2 + (q ? kSampleTail : -kSampleTail);
+            if (r >= before && r < before + tot) {
+                uint32_t acc = before;
+                int e = 0;
+                while (e < 3 && r >= acc + c[e]) acc += c[e++];
+                edge[q] = 4 * tid + e;
+                held[q] = c[e];
+            }
+        }
+        __syncthreads();
+        crowded = held[0] > kEdgeMany || held[1] > kEdgeMany;
     }
-    __syncthreads();
+    uint32_t end[2] = {0u, 0u};
+    if (crowded) {
+        // An eighth of the samples gives a window four of its deviations wide
+        // (4.4% of the similarities), the samples inside it the two ranks.
+        constexpr int N = E / 8, TAIL = kSampleTail * 46 / 128;    // (sqrt(8) = 2.83, 46 / 128 = 1 / 2.78)
+        uint32_t key[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) key[e] = fkey(v[e]);
+        uint32_t from, to;
+        two_ranks<N>(key, kSamples / 16 - TAIL, kSamples / 16 + TAIL, fkey(lo), fkey(hi), under[0], from, to);
+        if (tid < 4) held[tid] = 0u;
+        __syncthreads();
+        uint32_t below = 0u, at_from = 0u;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const uint32_t k = fkey(v[e]);
+            below += __popcll(__ballot(k < from));
+            at_from += __popcll(__ballot(k == from));
+            const unsigned long long m = __ballot(k > from && k < to);
+            if (m == 0ull) continue;
+            uint32_t at = 0u;
+            if (lane == 0) at = atomicAdd(&held[2], (uint32_t)__popcll(m));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + __popcll(m & ((1ull << lane) - 1ull));
+            if ((m >> lane & 1ull) && at < (uint32_t)kWinBins) hist[at] = k;
+        }
+        if (lane == 0) {
+            atomicAdd(&held[0], below);
+            atomicAdd(&held[1], at_from);
+        }
+        __syncthreads();
+        const uint32_t inside = held[2];
+        constexpr int NI = kWinBins / SMP_T;
+        uint32_t in[NI];
+#pragma unroll
+        for (int e = 0; e < NI; ++e) in[e] = tid + e * SMP_T < inside ? hist[tid + e * SMP_T] : 0xffffffffu;
+        // ranks among the samples between the two ends; outside them the end itself
+        const int base = (int)(held[0] + held[1]), r0 = kSamples / 2 - kSampleTail - base, r1 = r0 + 2 * kSampleTail;
+        two_ranks<NI>(in, r0, r1, from, to, under[1], end[0], end[1]);
+        if (inside > (uint32_t)kWinBins || r0 < 0) end[0] = from;
+        if (inside > (uint32_t)kWinBins || r1 >= (int)inside) end[1] = to;
+        if (r0 >= (int)inside) end[0] = to;
+        if (r1 < 0) end[1] = from;
+    }
     if (tid == 0) {
         const float w = (hi - lo) / (float)(kWinBins - 1);
         float a = lo + (float)edge[0] * w, b = lo + (float)(edge[1] + 1) * w;
-        if (a == 0.0f) a = -1.0e-30f;
-        if (b == 0.0f) b = 1.0e-30f;
+        const int ties = crowded;
+        if (ties) {
+            a = keyf(end[0]) + 0.0f;
+            b = keyf(end[1]) + 0.0f;
+        }
+        if (!ties && a == 0.0f) a = -1.0e-30f;
+        if (!ties && b == 0.0f) b = 1.0e-30f;
+        win->ties = ties;
         win->vlo = a;
         win->vhi = b;
         win->lo = fkey(a);
@@ -696,13 +827,12 @@ __global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n,
     }
 }
 
-// The window's first key and interval width: the sample's, or (whole) those
-// of the bounds of S.
-__device__ __forceinline__ void win_cut(const SelWin *win, const uint32_t *minmax, int whole, uint32_t &lo,
+// The first key and the interval width of the cut.
+__device__ __forceinline__ void win_cut(const SelWin *win, const uint32_t *minmax, int cut, uint32_t &lo,
                                         uint32_t &shift) {
     lo = win->lo;
     shift = win->shift;
-    if (whole) {
+    if (cut == CUT_WHOLE) {
         lo = minmax[0];
         const uint32_t span = minmax[1] - lo;
         const int bits = span ? 32 - __builtin_clz(span) : 0;
@@ -715,7 +845,7 @@ __device__ __forceinline__ void win_cut(const SelWin *win, const uint32_t *minma
 constexpr int RANK_T = 1024;      // one workgroup per list
 __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win, const SelSeg *segs,
                                                       const uint32_t *cand, uint32_t cap, uint32_t *whist,
-                                                      const uint32_t *minmax, int whole, const int32_t *bad) {
+                                                      const uint32_t *minmax, int cut, const int32_t *bad) {
     if (*bad) return;
     __shared__ uint32_t hist[kWinBins];
     __shared__ uint32_t wtot[RANK_T / 64];
@@ -726,14 +856,15 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     const uint32_t cnt = segs[sg].count < cap ? segs[sg].count : cap;
     const uint32_t *list = cand + (int64_t)sg * cap;
     uint32_t lo, shift;
-    win_cut(win, minmax, whole, lo, shift);
+    win_cut(win, minmax, cut, lo, shift);
+    const uint32_t hi = cut == CUT_AGAIN ? win->hi : 0xffffffffu;
     for (uint32_t e = tid; e < cnt; e += 8 * RANK_T) {
         uint32_t key[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) key[u] = e + u * RANK_T < cnt ? list[e + u * RANK_T] : 0u;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (e + u * RANK_T < cnt) atomicAdd(&hist[(key[u] - lo) >> shift], 1u);
+            if (e + u * RANK_T < cnt && key[u] >= lo && key[u] <= hi) atomicAdd(&hist[(key[u] - lo) >> shift], 1u);
     }
     __syncthreads();
     for (int b = tid; b < kWinBins; b += RANK_T)
@@ -742,10 +873,13 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     // keys below the window and in it: lane s of every wavefront has list s
     static_assert(kSegs == 64, "a list per lane");
     unsigned long long below = segs[lane].below, total = segs[lane].count;
+    unsigned long long at_lo = segs[lane].at[0], at_hi = segs[lane].at[1];
     const bool over = __any(segs[lane].count > cap);
     for (int off = 32; off >= 1; off >>= 1) {
         below += __shfl_xor(below, off, 64);
         total += __shfl_xor(total, off, 64);
+        at_lo += __shfl_xor(at_lo, off, 64);
+        at_hi += __shfl_xor(at_hi, off, 64);
     }
     constexpr int PER = kWinBins / RANK_T;
     uint32_t c[PER], own = 0u;
@@ -763,14 +897,34 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     __syncthreads();
     for (int w = 0; w < wave; ++w) incl += wtot[w];
     const uint32_t before = incl - own;
+    const uint32_t in_bin[2] = {win->bin[0], win->bin[1]}, in_rank[2] = {win->rank[0], win->rank[1]};
+    __syncthreads();                         // (they are rewritten below)
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const unsigned long long rank = st->rank[r];
-        if (over || rank < below || rank - below >= total) {
+        // in ascending order: below the window, equal to its lower end, set
+        // aside, equal to its upper end (the equal ones counted with ties only)
+        unsigned long long rank = st->rank[r];
+        if (cut == CUT_AGAIN) {
+            if (in_bin[r] == kNoBin) continue;
+            rank = below + at_lo + in_rank[r];
+        }
+        const bool under = rank < below;
+        rank -= below;
+        const bool lower = rank < at_lo;
+        if (!lower) rank -= at_lo;
+        const bool upper = !lower && rank >= total && rank - total < at_hi;
+        if (!under && (lower || upper)) {
+            if (tid == 0) {
+                st->prefix[r] = fkey(lower ? win->vlo : win->vhi);
+                win->bin[r] = kNoBin;
+            }
+            continue;
+        }
+        if (under || over || rank >= total) {
             if (tid == 0) win->miss = 1;
             continue;
         }
-        const uint32_t in = (uint32_t)(rank - below);
+        const uint32_t in = (uint32_t)rank;
         if (in >= before && in < incl) {
             uint32_t cum = before;
             int q = 0;
@@ -781,21 +935,34 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     }
 }
 
+// Before another cut of the lists (select null) or the select over S.
+__global__ __launch_bounds__(1024) void k_win_again(SelWin *win, uint32_t *whist, SelState *select) {
+    for (int b = threadIdx.x; b < kWinBins; b += blockDim.x) whist[b] = 0u;
+    if (threadIdx.x != 0) return;
+    win->miss = 0;
+    win->nlist = win->done[1] = win->done[2] = 0u;
+    win->kmin[0] = win->kmin[1] = 0xffffffffu;
+    win->kmax[0] = win->kmax[1] = 0u;
+    if (select != nullptr) select->prefix[0] = select->prefix[1] = 0u;
+}
+
 // Collects the keys of the two intervals; the last workgroup ranks them: ten
 // bits at a time below the interval's.
 __global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, const SelSeg *segs,
                                                      const uint32_t *cand, uint32_t cap, uint32_t *list2,
-                                                     const uint32_t *minmax, int whole, const int32_t *bad) {
+                                                     const uint32_t *minmax, int cut, const int32_t *bad) {
     if (*bad || win->miss) return;
     extern __shared__ uint32_t keys[];       // kWinList
-    __shared__ uint32_t hist[1024], wtot[RANK_T / 64], found[2], held, at0, bmin[2], bmax[2];
+    __shared__ uint32_t hist[1024], wtot[RANK_T / 64], found[3], held, at0, bmin[2], bmax[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sg = blockIdx.x;
     const uint32_t cnt = segs[sg].count < cap ? segs[sg].count : cap;
     const uint32_t *list = cand + (int64_t)sg * cap;
     const uint32_t b0 = win->bin[0], b1 = win->bin[1];
+    if (b0 == kNoBin && b1 == kNoBin) return;
     uint32_t lo, shift;
-    win_cut(win, minmax, whole, lo, shift);
+    win_cut(win, minmax, cut, lo, shift);
+    const uint32_t hi = cut == CUT_AGAIN ? win->hi : 0xffffffffu;
     if (tid == 0) held = 0u;
     if (tid < 2) {
         bmin[tid] = 0xffffffffu;
@@ -803,23 +970,28 @@ __global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, 
     }
     __syncthreads();
     uint32_t kmin[2] = {0xffffffffu, 0xffffffffu}, kmax[2] = {0u, 0u};
-    for (uint32_t e = tid; e < cnt; e += 8 * RANK_T) {
+    for (uint32_t e0 = 0u; e0 < cnt; e0 += 8 * RANK_T) {
+        const uint32_t e = e0 + (uint32_t)tid;
         uint32_t key[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) key[u] = e + u * RANK_T < cnt ? list[e + u * RANK_T] : 0u;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint32_t b = (key[u] - lo) >> shift;
-            if (e + u * RANK_T < cnt && (b == b0 || b == b1)) {
+            const bool hit = e + u * RANK_T < cnt && key[u] >= lo && key[u] <= hi && (b == b0 || b == b1);
+            const unsigned long long m = __ballot(hit);
+            if (m == 0ull) continue;
+            uint32_t at = 0u;
+            if (lane == 0) at = atomicAdd(&held, (uint32_t)__popcll(m));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + __popcll(m & ((1ull << lane) - 1ull));
+            if (!hit) continue;
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    if (b == (r ? b1 : b0)) {
-                        kmin[r] = min(kmin[r], key[u]);
-                        kmax[r] = max(kmax[r], key[u]);
-                    }
-                const uint32_t at = atomicAdd(&held, 1u);
-                if (at < (uint32_t)kWinList) keys[at] = key[u];
-            }
+            for (int r = 0; r < 2; ++r)
+                if (b == (r ? b1 : b0)) {
+                    kmin[r] = min(kmin[r], key[u]);
+                    kmax[r] = max(kmax[r], key[u]);
+                }
+            if (at < (uint32_t)kWinList) keys[at] = key[u];
         }
     }
 #pragma unroll
@@ -840,14 +1012,82 @@ __global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, 
     if (!last_block(&win->done[2])) return;
     const uint32_t nl = ld_dev(&win->nlist);
     if (nl > (uint32_t)kWinList) {
-        // many equal values (points on a grid): the intervals hold one key
-        // each, or the window has missed
-        if (tid == 0) {
-            for (int r = 0; r < 2; ++r) {
-                if (ld_dev(&win->kmin[r]) != ld_dev(&win->kmax[r])) win->miss = 1;
-                st->prefix[r] = ld_dev(&win->kmin[r]);
+        // Many keys in the intervals: one value only (points on a grid), or
+        // they are cut again, out of all lists, until one key is left; from
+        // more than kRecut keys on the select over S is faster.
+        uint32_t all = segs[lane].count < cap ? segs[lane].count : cap;
+        for (int off = 32; off >= 1; off >>= 1) all += __shfl_xor(all, off, 64);
+        const int first = b0 == kNoBin;          // a rank whose key is not known
+        const uint32_t k0 = ld_dev(&win->kmin[first]), k1 = ld_dev(&win->kmax[first]);
+        const bool one = b0 == b1 || first || b1 == kNoBin;   // one interval in question
+        if (all > kRecut && (!one || k0 != k1)) {
+            if (tid == 0) {
+                const int bits = k0 != k1 ? 32 - __builtin_clz(k1 - k0) : 0;
+                win->lo = k0;
+                win->hi = k1;
+                win->shift = bits > 12 ? bits - 12 : 0;
+                win->miss = one ? kCutAgain : 1;
             }
-            if (win->miss) st->prefix[0] = st->prefix[1] = 0u;
+            return;
+        }
+        // a few long lists where everything is set aside, else many short ones
+        const int per = cut == CUT_WHOLE ? RANK_T : 64;
+        bool both = b0 == b1;                    // the ranks still share an interval
+        uint32_t from1 = ld_dev(&win->kmin[1]), to1 = ld_dev(&win->kmax[1]), rank1 = win->rank[1];
+        for (int r = 0; r < 2; ++r) {
+            if ((r ? b1 : b0) == kNoBin) continue;
+            uint32_t from = r ? from1 : ld_dev(&win->kmin[0]), to = r ? to1 : ld_dev(&win->kmax[0]);
+            uint32_t rank = r ? rank1 : win->rank[0];
+            while (from != to) {
+                const int bits = 32 - __builtin_clz(to - from);
+                const uint32_t sh = bits > 11 ? bits - 11 : 0;
+                for (int b = tid; b < 2048; b += RANK_T) keys[b] = 0u;
+                __syncthreads();
+                for (int q = tid / per; q < kSegs; q += RANK_T / per) {
+                    const uint32_t c = segs[q].count < cap ? segs[q].count : cap;
+                    const uint32_t *l = cand + (int64_t)q * cap;
+                    for (uint32_t e = tid % per; e < c; e += 8 * per) {
+                        uint32_t key[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) key[u] = e + u * per < c ? l[e + u * per] : 0u;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (e + u * per < c && key[u] >= from && key[u] <= to) atomicAdd(&keys[(key[u] - from) >> sh], 1u);
+                    }
+                }
+                __syncthreads();
+                const uint32_t c0 = keys[2 * tid], own = c0 + keys[2 * tid + 1];
+                uint32_t incl = own;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t o = __shfl_up(incl, off, 64);
+                    if (lane >= off) incl += o;
+                }
+                if (lane == 63) wtot[wave] = incl;
+                __syncthreads();
+                for (int w = 0; w < wave; ++w) incl += wtot[w];
+                const uint32_t before = incl - own;
+                if (rank >= before && rank < incl) {
+                    const bool second = rank - before >= c0;
+                    found[0] = 2u * (uint32_t)tid + second;
+                    found[1] = before + (second ? c0 : 0u);
+                    found[2] = second ? own - c0 : c0;
+                }
+                __syncthreads();
+                // (rank 1 is not below rank 0)
+                both = both && r == 0 && rank1 - found[1] < found[2];
+                from += found[0] << sh;
+                rank -= found[1];
+                const uint32_t last = from + ((1u << sh) - 1u);
+                to = last < to ? last : to;
+                if (both) {
+                    from1 = from;
+                    to1 = to;
+                    rank1 -= found[1];
+                }
+                __syncthreads();
+            }
+            if (tid == 0) st->prefix[r] = from;
         }
         return;
     }
@@ -855,6 +1095,12 @@ __global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, 
     __syncthreads();
     for (int r = 0; r < 2; ++r) {
         uint32_t prefix = r ? b1 : b0, rank = win->rank[r];
+        if (prefix == kNoBin) continue;
+        const uint32_t least = ld_dev(&win->kmin[r]);
+        if (least == ld_dev(&win->kmax[r])) {    // one value
+            if (tid == 0) st->prefix[r] = least;
+            continue;
+        }
         for (int left = (int)shift; left > 0;) {
             const int bits = left < 10 ? left : 10;
             const int sh = left - bits;
@@ -1216,16 +1462,21 @@ extern "C" apx_status ap_similarity(apx_ctx *ctx, const float *X, int64_t n, int
     HIP_TRY(hipGetLastError(), "similarity gemm");
     PrefArgs pa{S, n, ld, pref_mode, pref_vec, pref_scalar, sel, mm, noise_seed, noise_rel, &dvals[1], bad, win, rep};
     const int noise_grid = (int)(n < 4096 ? n : 4096);
-    if (windowed) {
-        const int whole = n <= kWholeN;
-        k_win_count<<<kSegs, RANK_T, 0, s>>>(sel, win, segs, cand, (uint32_t)SL.cap, whist, mm, whole, bad);
+    uint32_t *list2 = reinterpret_cast<uint32_t *>(b + SL.o_l);
+    auto from_lists = [&](int cut) -> apx_status {
+        const uint32_t cap = (uint32_t)SL.cap;
+        k_win_count<<<kSegs, RANK_T, 0, s>>>(sel, win, segs, cand, cap, whist, mm, cut, bad);
         HIP_TRY(hipGetLastError(), "median count");
         constexpr size_t lds = sizeof(uint32_t) * kWinList;
         HIP_TRY(hipFuncSetAttribute((const void *)k_win_rank, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
                 "lds");
-        k_win_rank<<<kSegs, RANK_T, lds, s>>>(sel, win, segs, cand, (uint32_t)SL.cap,
-                                               reinterpret_cast<uint32_t *>(b + SL.o_l), mm, whole, bad);
+        k_win_rank<<<kSegs, RANK_T, lds, s>>>(sel, win, segs, cand, cap, list2, mm, cut, bad);
         HIP_TRY(hipGetLastError(), "median rank");
+        return APX_OK;
+    };
+    if (windowed) {
+        st = from_lists(n <= kWholeN ? CUT_WHOLE : CUT_WINDOW);
+        if (st != APX_OK) return st;
     }
     bool searched = windowed || !median;
     for (;;) {
@@ -1247,7 +1498,17 @@ extern "C" apx_status ap_similarity(apx_ctx *ctx, const float *X, int64_t n, int
         HIP_TRY(hipGetLastError(), "preference/noise");
         HIP_TRY(hipStreamSynchronize(s), "sync");
         if (rep->bad || !rep->miss) break;
-        searched = false;      // (nothing of the preferences has been written)
+        // (nothing of the preferences has been written)
+        const bool again = rep->miss == kCutAgain;
+        k_win_again<<<1, 1024, 0, s>>>(win, whist, again ? nullptr : sel);
+        HIP_TRY(hipGetLastError(), "median again");
+        if (again) {
+            // (a cut leaves 2^-12 of a range of keys: three at most)
+            st = from_lists(CUT_AGAIN);
+            if (st != APX_OK) return st;
+        } else {
+            searched = false;
+        }
     }
     // The bounds of the off-diagonal keys tell whether a similarity overflowed
     // (a key at or beyond the one of +inf or -inf: infinities and NaNs).
