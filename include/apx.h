@@ -179,9 +179,29 @@ apx_status apx_last_solve_info(apx_ctx *ctx, int32_t *implicit_iters, int32_t *e
  * APX_FALLBACK_A_LIST (a row's list of ever-positive responsibilities was
  * full).  APX_NOTE_R_OWNER (no fallback by itself) says that the implicit-A
  * pass let a row list break that owner rule, so a fallback of A would have
- * made R explicit too.  Diagnostic only; results do not depend on it. */
-enum { APX_FALLBACK_R_LIST = 1, APX_FALLBACK_A_LIST = 2, APX_FALLBACK_R_OWNER = 4, APX_NOTE_R_OWNER = 8 };
+ * made R explicit too.  APX_FALLBACK_WAIT: the workgroups of the one-launch
+ * solve did not all come to run within a few milliseconds (other work holds
+ * the chip) and the launched passes ran instead; after ap_solve_batched and
+ * pap_solve's Step 2, the same of instances that then ran in the streaming
+ * launch.  Diagnostic only; results do not depend on it. */
+enum {
+    APX_FALLBACK_R_LIST = 1,
+    APX_FALLBACK_A_LIST = 2,
+    APX_FALLBACK_R_OWNER = 4,
+    APX_NOTE_R_OWNER = 8,
+    APX_FALLBACK_WAIT = 16
+};
 apx_status apx_last_fallback(apx_ctx *ctx, int32_t *reasons);
+
+/* apx_set_give_up -- let the one-launch solves (ap_solve and ap_solve_batched
+ * up to 3072 points) give up their waits between workgroups at a chosen point,
+ * as they would if a workgroup did not come to run: at = iteration (0: before
+ * the first), -2: after the messages are written, -1 (default): nowhere.  For
+ * tests of what follows: a solve goes on in the launched passes, a batch in
+ * its streaming launch, from the caller's start; a warm start whose messages
+ * are already overwritten (-2) returns APX_EDEVICE.  Solves that need one
+ * workgroup wait for nothing. */
+apx_status apx_set_give_up(apx_ctx *ctx, int32_t at);
 
 /* apx_set_lean_scan -- the implicit-A pass leaves the ordinary columns out
  * of the exemplar decision of Algorithm 1 (argmax of a + r, Eqs. (2)-(4))

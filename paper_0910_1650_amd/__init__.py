@@ -78,6 +78,7 @@ SIGNATURES = {
     "apx_profile": (ctypes.c_int, [_P, ctypes.c_int]),
     "apx_set_graphs": (ctypes.c_int, [_P, ctypes.c_int]),
     "apx_set_lean_scan": (ctypes.c_int, [_P, ctypes.c_int]),
+    "apx_set_give_up": (ctypes.c_int, [_P, _I32]),
     "apx_last_lean_rescans": (ctypes.c_int, [_P, ctypes.POINTER(_I32)]),
     "apx_set_implicit": (ctypes.c_int, [_P, _I32, _I64]),
     "apx_set_implicit_a": (ctypes.c_int, [_P, _I32, _I64]),
@@ -376,14 +377,21 @@ def apx_last_solve_info(device=None) -> tuple[int, int, int]:
 
 
 APX_FALLBACK_R_LIST, APX_FALLBACK_A_LIST, APX_FALLBACK_R_OWNER, APX_NOTE_R_OWNER = 1, 2, 4, 8
+APX_FALLBACK_WAIT = 16
 
 
 def apx_last_fallback(device=None) -> int:
-    """Why the last ap_solve left an implicit form (OR of APX_FALLBACK_*; 0: it did not)."""
+    """Why the last ap_solve left an implicit form or its one launch (OR of APX_FALLBACK_*; 0: it did not)."""
     ctx = context(device)
     a = _I32()
     _check(ctx, lib().apx_last_fallback(ctx, ctypes.byref(a)), "apx_last_fallback")
     return a.value
+
+
+def apx_set_give_up(at: int, device=None) -> None:
+    """Tests: give up the waits of the one-launch solves at this iteration (-1: nowhere, -2: at the end)."""
+    ctx = context(device)
+    _check(ctx, lib().apx_set_give_up(ctx, at), "apx_set_give_up")
 
 
 def apx_set_lean_scan(enable: bool, device=None) -> None:

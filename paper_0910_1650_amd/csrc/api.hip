@@ -363,9 +363,10 @@ namespace {
 int res_rows(int64_t n) { return n <= 1024 ? 8 : 12; }
 
 // ap_solve in one launch (resident.hip) on the workspace w; APX_ENOTIMPL
-// (nothing written) where the size does not fit or the run did not end.
+// where the size does not fit or a wait was given up (gave_up): the launched
+// passes can then run from the caller's start.
 apx_status resident_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *R, float *A, int32_t warm,
-                          const apx_params *params, int32_t *idx, const IterWs &w, apx_result *res) {
+                          const apx_params *params, int32_t *idx, const IterWs &w, apx_result *res, bool *gave_up) {
     ResPlan pl{};
     if (!res_plan(n, ctx->num_cus, res_rows(n), &pl)) return APX_ENOTIMPL;
     // the exchange words (16 n bytes per member and a little) take the place
@@ -385,22 +386,22 @@ apx_status resident_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, f
     ResOut *out = reinterpret_cast<ResOut *>(static_cast<char *>(ctx->pinned) + 3072);
     d.out = out;
     res_exchange(pl, n, w.xst, &d);
-    out->done = 0;
+    out->done = out->wrote = 0;
     const float lam = params->damping;
     HIP_TRY(launch_res_zero(w.xst, pl.words, s), "exchange words");
     // a column-structured A_0 takes the undamped first step (damping 0 on R = 0)
     const hipError_t e = launch_resident(pl, d, lam, warm == APX_WARM_COLUMNS ? 0.0f : lam, params->max_iter,
-                                         params->conv_iter, s);
+                                         params->conv_iter, ctx->give_up, s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return APX_ENOTIMPL;
     }
     HIP_TRY(hipStreamSynchronize(s), "sync");
     if (out->done != 1) {
-        // a wait was given up: before the first iteration (-1), or on a cold
-        // start, the run can begin again; later a warm start may have lost
-        // its A_0 and R_0 to the rows already written
-        return warm == APX_COLD || out->done < 0
+        // a wait was given up: the run can begin again unless messages were
+        // written over a warm start's A_0 and R_0
+        *gave_up = true;
+        return warm == APX_COLD || !out->wrote
                    ? APX_ENOTIMPL
                    : set_err(ctx, APX_EDEVICE, "a wait between workgroups timed out");
     }
@@ -672,6 +673,13 @@ apx_status apx_last_fallback(apx_ctx *ctx, int32_t *reasons) {
     return APX_OK;
 }
 
+apx_status apx_set_give_up(apx_ctx *ctx, int32_t at) {
+    if (!ctx) return APX_EINVAL;
+    if (at < kGiveUpAtEnd) return set_err(ctx, APX_EINVAL, "give-up point must be >= %d", kGiveUpAtEnd);
+    ctx->give_up = at;
+    return APX_OK;
+}
+
 apx_status apx_set_lean_scan(apx_ctx *ctx, int enable) {
     if (!ctx) return APX_EINVAL;
     ctx->lean = enable != 0;
@@ -789,10 +797,11 @@ apx_status ap_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *
         implicit = r_ok;
     }
     // Explicit messages that fit in the register files: the whole run in one
-    // launch.  It writes R and A only at its end, so a run that did not end
-    // (a wait between its workgroups given up) goes on to the passes below.
+    // launch.  It writes R and A only at its end, so a run whose workgroups
+    // gave up waiting for each other goes on to the passes below.
+    bool gave_up = false;
     if (!implicit && !msg_rule && ctx->graphs && !ctx->prof) {
-        const apx_status rs = resident_solve(ctx, S, n, ld, R, A, warm, params, idx, w, res);
+        const apx_status rs = resident_solve(ctx, S, n, ld, R, A, warm, params, idx, w, res, &gave_up);
         if (rs != APX_ENOTIMPL) return rs;
     }
     HIP_TRY(launch_state_init(w.st, params->max_iter, params->conv_iter, lam, s, msg_rule ? 1 : 0,
@@ -808,7 +817,7 @@ apx_status ap_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, float *
     const int32_t *const ia_blk = ctx->ia_blk;
     int32_t imp_until = implicit ? INT32_MAX : 0;   // last iteration run with implicit R
     int32_t ia_until = imp_a ? INT32_MAX : 0;       // last iteration run with implicit A
-    int32_t fallback = 0;                           // imp_abort bits of the fallbacks
+    int32_t fallback = gave_up ? APX_FALLBACK_WAIT : 0;   // ... and imp_abort bits of the fallbacks
     if (implicit) {
         // parity 0 holds R_0 = 0: beta = 0 and empty lists
         const ImpLayout il = imp_layout(n);

@@ -235,8 +235,12 @@ constexpr int64_t kResMaxN = 3072;
 struct ResOut {
     double dpsim, expref;
     int32_t iterations, converged, n_exemplars;
-    int32_t done;        // 1 when the run ended by its stop rule, -1 when a wait was given up before iteration 1
+    int32_t done;        // 1 when the run ended by its stop rule (0: a wait was given up)
+    int32_t wrote;       // R or A may hold new messages
+    int32_t pad;
 };
+// ResArgs::give_up: the wait for the exemplar flags, after the messages are written
+constexpr int32_t kGiveUpAtEnd = -2;
 struct ResInst {
     const float *S;
     float *R, *A;        // outputs; A_0, R_0 on entry where load_a, load_r
@@ -265,12 +269,12 @@ struct ResTask {
 bool res_small(int64_t n);
 hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
                                  const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
-                                 int32_t conv_iter, hipStream_t s);
+                                 int32_t conv_iter, int32_t give_up, hipStream_t s);
 // Carves the exchange words of an instance from mem (pl.words words).
 void res_exchange(const ResPlan &pl, int64_t n, void *mem, ResInst *d);
 hipError_t launch_res_zero(void *mem, int64_t words, hipStream_t s);
 hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,
-                           int32_t conv_iter, hipStream_t s);
+                           int32_t conv_iter, int32_t give_up, hipStream_t s);
 
 // Finalize: labels and FP64 dpsim / expref.
 struct FinalArgs {
@@ -347,6 +351,7 @@ struct apx_ctx {
     int64_t implicit_a_min_n = 4096;  // smaller cold starts run explicit (faster there)
     int32_t last_ia_iters = 0;        // iterations of the last ap_solve run with implicit A
     int32_t last_fallback = 0;        // why the last ap_solve left an implicit form (imp_abort bits)
+    int32_t give_up = -1;             // waits of the one-launch solves given up on purpose (apx_set_give_up)
     bool lean = true;                 // lean scan in the implicit-A pass (off: every row forms r)
     int32_t last_lean_rescans = 0;    // rows of the last ap_solve whose ordinary columns decided
     // autotuner (tune.hip)

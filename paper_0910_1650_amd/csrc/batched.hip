@@ -752,7 +752,7 @@ bool res_batch_plan(const BatchSpec *spec, const std::vector<int32_t> &order, in
     B->o_lane = L.take(sizeof(int32_t) * B->lane.size());
     B->tab_bytes = L.off;
     B->o_out = L.take(sizeof(ResOut) * order.size());
-    B->o_abort = L.take(8);
+    B->o_abort = L.take(16);
     B->o_x0 = L.off;
     for (const ResPlan &p : B->plan) B->o_x.push_back(L.take(8 * (size_t)p.words));
     B->x_bytes = L.off - B->o_x0;
@@ -770,9 +770,12 @@ std::vector<int32_t> res_order(int32_t count, const BatchSpec *spec, bool small)
     return order;
 }
 
-// Solves the instances of the plan; results by instance number.
+// Solves the instances of the plan; results by instance number, done[j] set
+// for those that ran to their end.  The others can run elsewhere: their
+// workgroups gave up waiting for each other and left R and A as they were (or
+// the start is cold).
 apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spec, int32_t warm,
-                           const apx_params *params, apx_result *res) {
+                           const apx_params *params, apx_result *res, char *done) {
     hipStream_t s = ctx->stream;
     char *b = static_cast<char *>(ctx->ws) + ctx->ws_base;
     const size_t cnt = B.order.size();
@@ -804,13 +807,18 @@ apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spe
                                    reinterpret_cast<const ResTask *>(b + B.o_task),
                                    reinterpret_cast<const int32_t *>(b + B.o_lane),
                                    reinterpret_cast<unsigned long long *>(b + B.o_abort), params->damping,
-                                   params->max_iter, params->conv_iter, s)) ||
+                                   params->max_iter, params->conv_iter, ctx->give_up, s)) ||
         (e = hipMemcpyAsync(out.data(), b + B.o_out, sizeof(ResOut) * cnt, hipMemcpyDeviceToHost, s)) ||
         (e = hipStreamSynchronize(s)))
         return hip_err(ctx, e, "batched launch");
     for (size_t q = 0; q < cnt; ++q) {
         const ResOut &o = out[q];
-        if (o.done != 1) return set_err(ctx, APX_EDEVICE, "batched launch: a wait between workgroups timed out");
+        if (o.done != 1) {
+            if (o.wrote && warm != APX_COLD)
+                return set_err(ctx, APX_EDEVICE, "batched launch: a wait between workgroups timed out");
+            continue;
+        }
+        done[B.order[q]] = 1;
         apx_result &r = res[B.order[q]];
         std::memset(&r, 0, sizeof r);
         r.iterations = o.iterations;
@@ -862,15 +870,18 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
     const bool streamed = ctx->force_bwpc || ctx->force_bmin || getenv("APX_BATCH_WPC") || getenv("APX_BATCH_MIN_ROWS");
     std::vector<char> done(count, 0);
     int32_t left = count;
+    ctx->last_fallback = 0;
     for (bool small : {false, true}) {
         ResBatch B;
         if (streamed || !res_batch_plan(spec, res_order(count, spec, small), ctx->num_cus, &B)) continue;
         if (ctx->ws_external && ctx->ws_base + B.bytes > ctx->ws_bytes) continue;
         apx_status st = ws_reserve(ctx, ctx->ws_base + B.bytes);
-        if (st == APX_OK) st = res_batch_solve(ctx, B, spec, warm, params, res);
+        if (st == APX_OK) st = res_batch_solve(ctx, B, spec, warm, params, res, done.data());
         if (st != APX_OK) return st;
-        for (int32_t j : B.order) done[j] = 1;
-        left -= (int32_t)B.order.size();
+        for (int32_t j : B.order) {
+            if (done[j]) --left;
+            else ctx->last_fallback = APX_FALLBACK_WAIT;
+        }
     }
     if (left == 0) return APX_OK;
     if (left < count) {

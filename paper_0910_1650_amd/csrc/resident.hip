@@ -59,10 +59,15 @@ constexpr int kSmallGroups = 6;
 constexpr int kRedLanes = 8;      // lanes that finish one column's sum
 constexpr int kMaxRows = 64;      // rows a member can own (one bit each, kRedLanes threads each)
 static_assert(kMaxRows * kRedLanes <= RT, "threads of the reduction");
-// polls of one word before a wait is given up (each takes about a
-// microsecond; a legitimate wait is one iteration of another member)
+// Polls of one word before a wait is given up (each takes about a
+// microsecond; a legitimate wait is one iteration of another member).
 constexpr uint32_t kPollLimit = 1u << 21;
-
+// Until the members have met once, one of them may not run at all: other work
+// holds its compute unit, which may itself be waiting for this one to end (a
+// solve of another process).  That wait is short, since giving up is cheap
+// there: nothing has been written and the launched passes need no company.
+constexpr uint32_t kMeetLimit = 1u << 12;
+// A batch's workgroups have all met when they wait for earlier instances.
 constexpr uint32_t kArriveLimit = 1u << 28;
 
 typedef unsigned long long u64;
@@ -183,7 +188,8 @@ struct ResArgs {
     const ResInst *insts;     // a batch's instances
     const ResTask *tasks;     // workgroup b runs tasks [lane[b], lane[b+1]) in order
     const int32_t *lane;
-    u64 *abort;               // set when a wait of a batch was given up
+    u64 *abort;               // a batch's words: [0] set when a wait was given up, [1] workgroups that run
+    int32_t give_up;          // iteration whose waits are given up at once (none: -1; kGiveUpAtEnd: the labels')
     float lam, lam0;          // damping; damping of the first responsibility step
     int32_t max_iter, conv_iter;
 };
@@ -316,6 +322,8 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
     float lu = p.lam0, lo = 1.0f - p.lam0;    // damping of the next responsibility step
     float la = 1.0f, oa = 0.0f;               // ... availability step: A_0 stays as it is at t = 0
     bool converged = false;
+    uint32_t limit = kMeetLimit;              // polls of the waits of the exchanges
+    const int give_up = p.give_up;
     int t = 0;
     __syncthreads();
 
@@ -549,7 +557,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
 #pragma unroll
                         for (int x = 0; x < 4; ++x) off |= w[x] ^ sign;
                         if ((long long)off >= 0) break;
-                        if (++polls > kPollLimit) {
+                        if (++polls > limit) {
                             bad = true;
                             break;
                         }
@@ -591,7 +599,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
                 for (int u = 0; u < NU; ++u)
                     if (tid + u * RT < n) ready &= (uint32_t)(w[u] >> 33) == (uint32_t)(t + 1);
                 if (ready) break;
-                if (++polls > kPollLimit) {
+                if (++polls > limit) {
                     *L.fail = 1;
                     break;
                 }
@@ -617,20 +625,21 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
             if (enow != eprev) L.cnt[nu] = 1;
             eprev = enow;
         }
-        if (tid == 0) L.cnt[nu ^ 1] = 0;
-        __syncthreads();
-        if (*L.fail) {
-            // In the first exchange a member may not run yet, while other
-            // work holds the chip.  One that gives up there publishes no
-            // iteration 1, so no member ends and no row has been written.
-            if (first && tid == 0) d.out->done = -1;
-            return false;
+        limit = kPollLimit;
+        if (tid == 0) {
+            L.cnt[nu ^ 1] = 0;
+            if (M > 1 && t == give_up) *L.fail = 1;
         }
+        __syncthreads();
+        if (*L.fail) return false;
         // the set of iteration t (none at t = 0) against the one before
         if (!first) run = (t > 1 && !L.cnt[nu]) ? run + 1 : 1;
     }
 
-    // ---- R_T, A_T
+    // ---- R_T, A_T.  From here on a wait given up leaves messages that are no
+    // start any more, and says so (wrote).  One given up above does not: a
+    // member that writes waits below for the flags of all, so where one has
+    // left the loop early, every member that wrote gives up there.
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < RPW; ++q) {
@@ -682,8 +691,12 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         for (int k = tid; k < n; k += RT) L.t[k] = L.e[k] ? 0.0f : kNegInf;
     }
     for (int k = n + tid; k < NC; k += RT) L.t[k] = kNegInf;
+    if (M > 1 && give_up == kGiveUpAtEnd) *L.fail = 1;
     __syncthreads();
-    if (*L.fail) return false;
+    if (*L.fail) {
+        if (tid == 0) d.out->wrote = 1;
+        return false;
+    }
     u64 *con = d.pair + 3 * (int64_t)n;
 #pragma unroll
     for (int q = 0; q < RPW; ++q) {
@@ -760,7 +773,10 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         }
         __syncthreads();
     }
-    if (*L.fail) return false;
+    if (*L.fail) {
+        if (tid == 0) d.out->wrote = 1;
+        return false;
+    }
     if (tid == 0) {
         ResOut o;
         o.dpsim = sh[0];
@@ -769,6 +785,8 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         o.converged = converged;
         o.n_exemplars = L.cnt[0];
         o.done = 1;
+        o.wrote = 1;
+        o.pad = 0;
         *d.out = o;
     }
     return true;
@@ -806,6 +824,29 @@ __device__ __forceinline__ bool all_arrived(const ResInst &d, int rank, const u6
     return ok;
 }
 
+// True when every workgroup of the grid runs: from then on a wait between
+// them ends.  Otherwise nothing has been started, and nothing is.
+__device__ __forceinline__ bool grid_met(const ResArgs &p, char *lds) {
+    int *stop = reinterpret_cast<int *>(lds);
+    if (threadIdx.x == 0) {
+        *stop = 0;
+        atomicAdd(p.abort + 1, 1ull);
+        uint32_t polls = 0u;
+        while (p.give_up == 0 || ld_dev(p.abort + 1) < (u64)gridDim.x) {
+            __builtin_amdgcn_s_sleep(8);
+            if (p.give_up == 0 || ld_dev(p.abort) != 0ull || ++polls > kMeetLimit) {
+                st_dev(p.abort, 1ull);
+                *stop = 1;
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    const bool ok = *stop == 0;
+    __syncthreads();
+    return ok;
+}
+
 // Many instances of uneven size: workgroup b runs its tasks in turn.  The
 // tasks of every workgroup are in one order of the instances, so the first
 // instance not yet done always has all of its members at work on it.
@@ -813,6 +854,7 @@ template <bool SMALL>
 __global__ __launch_bounds__(RT) void k_resident_batch(ResArgs p) {
     extern __shared__ char lds[];
     const int q1 = p.lane[blockIdx.x + 1];
+    if (!grid_met(p, lds)) return;
     for (int q = p.lane[blockIdx.x]; q < q1; ++q) {
         const ResTask tk = p.tasks[q];
         const ResInst d = p.insts[tk.inst];
@@ -917,8 +959,9 @@ bool res_small(int64_t n) { return n <= 256 * kSmallChunks; }
 
 hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
                                  const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
-                                 int32_t conv_iter, hipStream_t s) {
+                                 int32_t conv_iter, int32_t give_up, hipStream_t s) {
     ResArgs a{};
+    a.give_up = give_up;
     a.insts = insts;
     a.tasks = tasks;
     a.lane = lane;
@@ -935,8 +978,9 @@ hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst
 }
 
 hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,
-                           int32_t conv_iter, hipStream_t s) {
+                           int32_t conv_iter, int32_t give_up, hipStream_t s) {
     ResArgs a{};
+    a.give_up = give_up;
     a.one = d;
     a.lam = lam;
     a.lam0 = lam0;
