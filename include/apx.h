@@ -224,8 +224,9 @@ apx_status apx_last_lean_rescans(apx_ctx *ctx, int32_t *rows);
 /* apx_set_graphs -- run the iteration loop of ap_solve without the host
  * launching its kernels one by one (enable = 1, the default; the environment
  * variable APX_GRAPHS=0 turns it off at context creation): explicit messages
- * of up to 3072 points in one cooperative launch that holds them in
- * registers, other runs as a captured HIP graph, replayed on a private
+ * of up to 3072 points in one launch that holds them in registers (such
+ * launches of several contexts share the device as far as its compute units
+ * go), other runs as a captured HIP graph, replayed on a private
  * stream of the context that is ordered after the context stream with an
  * event.  enable = 0 launches every kernel from the host.  Results are
  * identical either way. */
@@ -455,7 +456,7 @@ typedef struct {
 /*
  * ap_solve_batched -- Algorithm 1 on `count` independent instances of uneven
  * size (inst: host array).  Instances of up to 3072 points run in one
- * cooperative launch per class of sizes (up to 1024 points, above) with their
+ * launch per class of sizes (up to 1024 points, above) with their
  * messages in registers: an instance gets as many workgroups as its rows
  * need, all instances run at once where they fit the chip, else in turns
  * largest first; their results are those of ap_solve with explicit messages,

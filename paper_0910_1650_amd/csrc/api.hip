@@ -388,15 +388,18 @@ apx_status resident_solve(apx_ctx *ctx, const float *S, int64_t n, int64_t ld, f
     res_exchange(pl, n, w.xst, &d);
     out->done = out->wrote = 0;
     const float lam = params->damping;
-    HIP_TRY(launch_res_zero(w.xst, pl.words, s), "exchange words");
-    // a column-structured A_0 takes the undamped first step (damping 0 on R = 0)
-    const hipError_t e = launch_resident(pl, d, lam, warm == APX_WARM_COLUMNS ? 0.0f : lam, params->max_iter,
-                                         params->conv_iter, ctx->give_up, s);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return APX_ENOTIMPL;
+    {
+        const CuHold hold(ctx->device, s, pl.members, ctx->num_cus);
+        HIP_TRY(launch_res_zero(w.xst, pl.words, s), "exchange words");
+        // a column-structured A_0 takes the undamped first step (damping 0 on R = 0)
+        const hipError_t e = launch_resident(pl, d, lam, warm == APX_WARM_COLUMNS ? 0.0f : lam, params->max_iter,
+                                             params->conv_iter, ctx->give_up, s);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return APX_ENOTIMPL;
+        }
+        HIP_TRY(hipStreamSynchronize(s), "sync");
     }
-    HIP_TRY(hipStreamSynchronize(s), "sync");
     if (out->done != 1) {
         // a wait was given up: the run can begin again unless messages were
         // written over a warm start's A_0 and R_0
@@ -541,6 +544,7 @@ apx_status apx_create(apx_ctx **out, int device, void *hip_stream) {
     const char *tf = getenv("APX_TUNE_FILE");
     if (tf && tf[0]) (void)apx_tune_load(ctx, tf);   // a missing or foreign file leaves the defaults
     ctx->err.clear();
+    cu_contexts(device, 1);
     *out = ctx;
     return APX_OK;
 }
@@ -559,6 +563,7 @@ void apx_destroy(apx_ctx *ctx) {
     if (ctx->ws && !ctx->ws_external) (void)hipFree(ctx->ws);
     if (ctx->dflag) (void)hipFree(ctx->dflag);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    cu_contexts(ctx->device, -1);
     delete ctx;
 }
 

@@ -276,6 +276,25 @@ hipError_t launch_res_zero(void *mem, int64_t words, hipStream_t s);
 hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,
                            int32_t conv_iter, int32_t give_up, hipStream_t s);
 
+// Holds compute units for a launch whose workgroups wait for each other, from
+// before the launch until its stream has been synchronised.  Such launches of
+// one process share a device as long as their workgroups, rounded up to whole
+// rounds over its eight XCDs (a launch deals its workgroups to them in turn),
+// find a unit each; the next one waits here, in order of arrival.  Cooperative
+// launches would be run one after another instead, however small: four threads
+// with a context each that solve 300 points took 288 us per solve so, 88
+// sharing the chip.  Streams and kernels that do not wait for others need no
+// hold: they end by themselves.
+struct CuHold {
+    CuHold(int device, hipStream_t s, int workgroups, int num_cus);
+    ~CuHold();
+    CuHold(const CuHold &) = delete;
+    CuHold &operator=(const CuHold &) = delete;
+    int device, units;
+};
+// Contexts of a device: +1 when one is created, -1 when it is destroyed.
+void cu_contexts(int device, int change);
+
 // Finalize: labels and FP64 dpsim / expref.
 struct FinalArgs {
     const float *S;

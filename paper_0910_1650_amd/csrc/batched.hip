@@ -801,6 +801,7 @@ apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spe
     // the results and the exchange words start at zero
     hipError_t e;
     std::vector<ResOut> out(cnt);
+    const CuHold hold(ctx->device, s, B.grid, ctx->num_cus);
     if ((e = hipMemcpyAsync(b, tab.data(), B.tab_bytes, hipMemcpyHostToDevice, s)) ||
         (e = launch_res_zero(b + B.o_out, (int64_t)((B.o_x0 - B.o_out + B.x_bytes) / 8), s)) ||
         (e = launch_resident_batch(B.small, B.grid, B.lds, reinterpret_cast<const ResInst *>(b + B.o_tab),
@@ -978,6 +979,8 @@ apx_status batched_stream(apx_ctx *ctx, int32_t count, const BatchSpec *spec, in
         k_batch_zero<<<zgrid, 256, 0, s>>>(ddesc, 1);
         if ((e = hipGetLastError())) return hip_err(ctx, e, "R_0");
     }
+    // (as many workgroups as fit: the whole chip)
+    const CuHold hold(ctx->device, s, ctx->num_cus, ctx->num_cus);
     PersistArgs pa{ddesc, dtasks, dlane, dbars, dfail, params->damping, warm};
     if ((e = persist_launch(J, pa, P.G, s))) return hip_err(ctx, e, "persistent batch launch");
     k_batch_fix_r<<<zgrid, 256, 0, s>>>(ddesc);

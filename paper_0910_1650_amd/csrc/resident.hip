@@ -1,8 +1,8 @@
 // resident.hip -- Algorithm 1 (Section 2) with the messages held on the chip.
 //
 // Up to kResMaxN points, S, R and A of a solve (12 bytes per element) fit in
-// the vector registers of the compute units (128 MB), so one cooperative
-// launch runs the whole solve: the matrices are read once and written once,
+// the vector registers of the compute units (128 MB), so one launch of
+// workgroups that all run at once runs the whole solve: the matrices are read once and written once,
 // and an iteration moves only column vectors between workgroups.  The
 // streaming passes (ap_iter.hip) take two launches and 20 bytes per element
 // and iteration: 13.8 us at n = 500, 29 at 2000, 49 at 3001; here an
@@ -31,8 +31,11 @@
 // The sums are those of the streaming passes: rows are grouped as there (at
 // most 512 groups of consecutive rows, each summed in FP32 in row order) and
 // the groups are added in FP64, so results agree with the launched passes.
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
+#include <mutex>
 
 #include "apx_internal.h"
 
@@ -881,6 +884,21 @@ __global__ __launch_bounds__(RT) void k_resident_batch(ResArgs p) {
     }
 }
 
+// Admission of launches whose workgroups wait for each other to the compute
+// units of a device, in order of arrival.
+struct CuGate {
+    std::mutex m;
+    std::condition_variable cv;
+    uint64_t next = 0, serving = 0;
+    int used = 0;
+    std::atomic<int> contexts{0};
+};
+constexpr int kGates = 64;
+CuGate &gate_of(int device) {
+    static CuGate *const gates = new CuGate[kGates];    // (never destroyed: threads may outlive main)
+    return gates[device & (kGates - 1)];
+}
+
 // Zeroes the exchange words (8 bytes each) of the instance.
 __global__ __launch_bounds__(256) void k_res_zero(u64 *p, int64_t words) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256) p[i] = 0ull;
@@ -969,12 +987,13 @@ hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst
     a.lam = a.lam0 = lam;
     a.max_iter = max_iter;
     a.conv_iter = conv_iter;
+    // (a plain launch; see CuHold)
     const void *f = small ? reinterpret_cast<const void *>(&k_resident_batch<true>)
                           : reinterpret_cast<const void *>(&k_resident_batch<false>);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(f, dim3(grid), dim3(RT), args, (unsigned)lds, s);
+    return hipLaunchKernel(f, dim3(grid), dim3(RT), args, (unsigned)lds, s);
 }
 
 hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float lam0, int32_t max_iter,
@@ -996,7 +1015,33 @@ hipError_t launch_resident(const ResPlan &pl, const ResInst &d, float lam, float
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
     if (e != hipSuccess) return e;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(f, dim3(pl.members), dim3(RT), args, (unsigned)pl.lds, s);
+    return hipLaunchKernel(f, dim3(pl.members), dim3(RT), args, (unsigned)pl.lds, s);
+}
+
+void cu_contexts(int device, int change) { gate_of(device).contexts += change; }
+
+CuHold::CuHold(int device, hipStream_t s, int workgroups, int num_cus) : device(device) {
+    CuGate &g = gate_of(device);
+    // Work the stream still has to do is not waited for inside the gate,
+    // where it would keep out other contexts.
+    if (g.contexts > 1 && hipStreamQuery(s) == hipErrorNotReady) (void)hipStreamSynchronize(s);
+    units = (workgroups + 7) & ~7;
+    std::unique_lock<std::mutex> l(g.m);
+    const uint64_t mine = g.next++;
+    g.cv.wait(l, [&] { return mine == g.serving && (g.used == 0 || g.used + units <= num_cus); });
+    ++g.serving;
+    g.used += units;
+    l.unlock();
+    g.cv.notify_all();
+}
+
+CuHold::~CuHold() {
+    CuGate &g = gate_of(device);
+    {
+        std::lock_guard<std::mutex> l(g.m);
+        g.used -= units;
+    }
+    g.cv.notify_all();
 }
 
 }  // namespace apx
