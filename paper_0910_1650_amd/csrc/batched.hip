@@ -840,9 +840,17 @@ apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spe
 }  // namespace
 
 size_t batched_ws_bytes(int32_t count, const BatchSpec *spec, int num_cus) {
-    // an upper bound: the plan at the largest workgroups per CU and the
-    // largest teams (one row per member at least)
+    // an upper bound: the streaming plan at the largest workgroups per CU and
+    // the largest teams (one row per member at least), of all instances and of
+    // those the other launches leave (fewer instances get larger teams)
     size_t bytes = make_plan(count, spec, num_cus, kMaxWpc, 1).bytes;
+    std::vector<BatchSpec> rest;
+    for (int32_t j = 0; j < count; ++j)
+        if (spec[j].n > kResMaxN) rest.push_back(spec[j]);
+    if (!rest.empty() && (int32_t)rest.size() < count) {
+        const size_t r = make_plan((int32_t)rest.size(), rest.data(), num_cus, kMaxWpc, 1).bytes;
+        bytes = r > bytes ? r : bytes;
+    }
     for (bool small : {false, true}) {
         ResBatch B;
         if (res_batch_plan(spec, res_order(count, spec, small), num_cus, &B) && B.bytes > bytes) bytes = B.bytes;
@@ -851,6 +859,38 @@ size_t batched_ws_bytes(int32_t count, const BatchSpec *spec, int num_cus) {
 }
 
 namespace {
+// The plan of the streaming batch, its workspace reserved: tuned for this batch
+// shape if known (apx_autotune_batched), the environment (APX_BATCH_WPC,
+// APX_BATCH_MIN_ROWS) over that, the tuner's candidate while it times.  A
+// workspace that cannot grow (the caller's, or one with data of the running
+// call below ws_base) gets smaller teams where it does not hold the plan's.
+apx_status stream_plan(apx_ctx *ctx, int32_t count, const BatchSpec *spec, BatchPlan *P) {
+    int64_t max_n = 0;
+    for (int j = 0; j < count; ++j) max_n = spec[j].n > max_n ? spec[j].n : max_n;
+    const int J = (int)((max_n + 4 * BT - 1) / (4 * BT));
+    if (J > 12) return set_err(ctx, APX_ENOTIMPL, "batched instances are limited to n <= %d", 12 * 4 * BT);
+    int wpc = occupancy_of(J);
+    if (wpc < 1) return set_err(ctx, APX_EDEVICE, "no occupancy for the batched kernel");
+    int cap = kMaxWpc, min_rows = kMinMemberRows;
+    const BatchTune *bt = find_batch_tune(ctx, count, max_n);
+    if (bt) {
+        cap = bt->wpc;
+        min_rows = bt->min_rows;
+    }
+    cap = env_int("APX_BATCH_WPC", cap, 1, kMaxWpc);
+    min_rows = env_int("APX_BATCH_MIN_ROWS", min_rows, 1, 1 << 20);
+    if (ctx->force_bwpc) cap = ctx->force_bwpc;
+    if (ctx->force_bmin) min_rows = ctx->force_bmin;
+    wpc = wpc < cap ? wpc : cap;
+    *P = make_plan(count, spec, ctx->num_cus, wpc, min_rows);
+    const bool fixed = ctx->ws_external || ctx->ws_base > 0;
+    while (fixed && ctx->ws_base + P->bytes > ctx->ws_bytes && min_rows < max_n) {
+        min_rows *= 4;
+        *P = make_plan(count, spec, ctx->num_cus, wpc, min_rows);
+    }
+    return ws_reserve(ctx, ctx->ws_base + P->bytes);
+}
+
 // The streaming batch: tables, initial state, one persistent cooperative
 // launch, then R_T and the labels.
 apx_status batched_stream(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int32_t warm, const apx_params *params,
@@ -867,36 +907,59 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
         return set_err(ctx, APX_ENOTIMPL, "batched instances are limited to n <= %d", 12 * 4 * BT);
     // Instances whose messages fit in registers go first, one launch for each
     // class of sizes; a forced or hand-set plan of the launch below (the tuner,
-    // APX_BATCH_WPC, APX_BATCH_MIN_ROWS) keeps every instance there.
+    // APX_BATCH_WPC, APX_BATCH_MIN_ROWS) keeps every instance there, and so
+    // does a workspace without room for theirs.
     const bool streamed = ctx->force_bwpc || ctx->force_bmin || getenv("APX_BATCH_WPC") || getenv("APX_BATCH_MIN_ROWS");
-    std::vector<char> done(count, 0);
-    int32_t left = count;
+    const bool fixed = ctx->ws_external || ctx->ws_base > 0;
     ctx->last_fallback = 0;
-    for (bool small : {false, true}) {
-        ResBatch B;
-        if (streamed || !res_batch_plan(spec, res_order(count, spec, small), ctx->num_cus, &B)) continue;
-        if (ctx->ws_external && ctx->ws_base + B.bytes > ctx->ws_bytes) continue;
-        apx_status st = ws_reserve(ctx, ctx->ws_base + B.bytes);
-        if (st == APX_OK) st = res_batch_solve(ctx, B, spec, warm, params, res, done.data());
-        if (st != APX_OK) return st;
-        for (int32_t j : B.order) {
-            if (done[j]) --left;
-            else ctx->last_fallback = APX_FALLBACK_WAIT;
-        }
+    std::vector<char> done(count, 0);
+    ResBatch cls[2];
+    bool use[2];
+    for (int c = 0; c < 2; ++c) {
+        use[c] = !streamed && res_batch_plan(spec, res_order(count, spec, c == 1), ctx->num_cus, &cls[c]) &&
+                 !(fixed && ctx->ws_base + cls[c].bytes > ctx->ws_bytes);
+        if (use[c])
+            for (int32_t j : cls[c].order) done[j] = 1;
     }
-    if (left == 0) return APX_OK;
-    if (left < count) {
-        std::vector<BatchSpec> rest;
+    std::vector<int32_t> left;
+    std::vector<BatchSpec> rest;
+    auto collect = [&]() {
+        left.clear();
+        rest.clear();
         for (int32_t j = 0; j < count; ++j)
-            if (!done[j]) rest.push_back(spec[j]);
-        std::vector<apx_result> rr(rest.size());
-        const apx_status st = batched_stream(ctx, left, rest.data(), warm, params, rr.data());
-        if (st == APX_OK)
-            for (int32_t j = 0, q = 0; j < count; ++j)
-                if (!done[j]) res[j] = rr[q++];
-        return st;
+            if (!done[j]) {
+                left.push_back(j);
+                rest.push_back(spec[j]);
+            }
+    };
+    // Room for all that will run is found before anything does: a call that
+    // does not fit leaves every output as it was.
+    collect();
+    if (!rest.empty()) {
+        BatchPlan P;
+        const apx_status st = stream_plan(ctx, (int32_t)rest.size(), rest.data(), &P);
+        if (st != APX_OK) return st;
     }
-    return batched_stream(ctx, count, spec, warm, params, res);
+    for (int c = 0; c < 2; ++c)
+        if (use[c]) {
+            const apx_status st = ws_reserve(ctx, ctx->ws_base + cls[c].bytes);
+            if (st != APX_OK) return st;
+        }
+    for (int c = 0; c < 2; ++c) {
+        if (!use[c]) continue;
+        for (int32_t j : cls[c].order) done[j] = 0;
+        const apx_status st = res_batch_solve(ctx, cls[c], spec, warm, params, res, done.data());
+        if (st != APX_OK) return st;
+        for (int32_t j : cls[c].order)
+            if (!done[j]) ctx->last_fallback = APX_FALLBACK_WAIT;
+    }
+    collect();
+    if (rest.empty()) return APX_OK;
+    std::vector<apx_result> rr(rest.size());
+    const apx_status st = batched_stream(ctx, (int32_t)rest.size(), rest.data(), warm, params, rr.data());
+    if (st == APX_OK)
+        for (size_t q = 0; q < left.size(); ++q) res[left[q]] = rr[q];
+    return st;
 }
 
 namespace {
@@ -906,25 +969,8 @@ apx_status batched_stream(apx_ctx *ctx, int32_t count, const BatchSpec *spec, in
     int64_t max_n = 0;
     for (int j = 0; j < count; ++j) max_n = spec[j].n > max_n ? spec[j].n : max_n;
     const int J = (int)((max_n + 4 * BT - 1) / (4 * BT));
-    if (J > 12) return set_err(ctx, APX_ENOTIMPL, "batched instances are limited to n <= %d", 12 * 4 * BT);
-    int wpc = occupancy_of(J);
-    if (wpc < 1) return set_err(ctx, APX_EDEVICE, "no occupancy for the batched kernel");
-    // plan: tuned for this batch shape if known (apx_autotune_batched), the
-    // environment (APX_BATCH_WPC, APX_BATCH_MIN_ROWS) over that, the tuner's
-    // candidate while it times
-    int cap = kMaxWpc, min_rows = kMinMemberRows;
-    const BatchTune *bt = find_batch_tune(ctx, count, max_n);
-    if (bt) {
-        cap = bt->wpc;
-        min_rows = bt->min_rows;
-    }
-    cap = env_int("APX_BATCH_WPC", cap, 1, kMaxWpc);
-    min_rows = env_int("APX_BATCH_MIN_ROWS", min_rows, 1, 1 << 20);
-    if (ctx->force_bwpc) cap = ctx->force_bwpc;
-    if (ctx->force_bmin) min_rows = ctx->force_bmin;
-    wpc = wpc < cap ? wpc : cap;
-    BatchPlan P = make_plan(count, spec, ctx->num_cus, wpc, min_rows);
-    apx_status st = ws_reserve(ctx, ctx->ws_base + P.bytes);
+    BatchPlan P;
+    const apx_status st = stream_plan(ctx, count, spec, &P);
     if (st != APX_OK) return st;
     char *b = static_cast<char *>(ctx->ws) + ctx->ws_base;
 
