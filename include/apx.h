@@ -280,11 +280,15 @@ apx_status apx_tune_set_form(apx_ctx *ctx, int64_t n, int32_t form);
 apx_status apx_tune_get_form(apx_ctx *ctx, int64_t n, int32_t *form, double *ms);
 /* apx_autotune_batched -- time the plans of the streaming batched launch
  * (instances above 3072 points of ap_solve_batched, pap_solve's Step 2) for a
- * batch of `count` instances of
- * sizes[j] points (host) on scratch instances of those sizes (allocated and
- * freed: 3 n x n matrices each), over workgroups per compute unit 1..4 and
- * 2, 8 or 32 rows at least per team member, and keep the fastest for
- * batches of that shape (the bit lengths of count and of the largest n).
+ * batch of `count` instances of sizes[j] points (host), over workgroups per
+ * compute unit 1..4 and 2, 8 or 32 rows at least per team member, and keep
+ * the fastest.  A batch with instances above 3072 points is timed on those
+ * alone, on scratch instances of their sizes (allocated and freed: 3 n x n
+ * matrices each), and the plan is kept for calls that stream as many of that
+ * size (the bit lengths of their number and of the largest n), whatever small
+ * instances come with them.  A batch without any needs no plan: its calls do
+ * not stream; one is timed on all of it and kept for the calls that stream
+ * all the same (no room in the workspace, a wait given up).
  * Outputs (nullable): the pick and its time for 12 iterations.  Plans group
  * the column partial sums differently, so a tuned plan changes results at
  * the rounding level. */

@@ -1087,11 +1087,23 @@ extern "C" apx_status apx_autotune_batched(apx_ctx *ctx, int32_t count, const in
                                            int32_t *min_rows_out, double *ms_out) {
     if (!ctx) return APX_EINVAL;
     if (count < 1 || !sizes) return set_err(ctx, APX_EINVAL, "need count >= 1 and sizes");
+    // A call with this batch streams the instances above kResMaxN, and looks a
+    // plan up for those: they are what is timed.  Without one the plan is that
+    // of the whole batch, for when all of it streams.
+    std::vector<int64_t> streamed;
+    for (int j = 0; j < count; ++j) {
+        if (sizes[j] < 2 || sizes[j] > 12 * 4 * BT)
+            return set_err(ctx, APX_EINVAL, "instance %d: need 2 <= n <= %d", j, 12 * 4 * BT);
+        if (sizes[j] > kResMaxN) streamed.push_back(sizes[j]);
+    }
+    if (!streamed.empty()) {
+        sizes = streamed.data();
+        count = (int32_t)streamed.size();
+    }
     int64_t max_n = 0, total = 0;
     std::vector<int64_t> lds(count), offs(count);
     for (int j = 0; j < count; ++j) {
         const int64_t n = sizes[j];
-        if (n < 2 || n > 12 * 4 * BT) return set_err(ctx, APX_EINVAL, "instance %d: need 2 <= n <= %d", j, 12 * 4 * BT);
         max_n = n > max_n ? n : max_n;
         lds[j] = (n + 3) & ~int64_t(3);
         offs[j] = total;
