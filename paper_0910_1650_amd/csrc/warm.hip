@@ -242,10 +242,12 @@ __device__ __forceinline__ void row_tail(Each each, const uint32_t *keys, float 
 constexpr int ST_T = 512;
 constexpr int kBins = 2048, kCand = 1024;
 static_assert(kBins == 4 * ST_T, "four intervals per thread");
-// Keys of an interval that are still ranked by counting (64: 2 us; 256: 25).
-// Evenly spread rows of 65536 points have about a hundred in one, and another
-// cut of such a row costs more than counting them.
-__device__ __forceinline__ int many_keys(int n) { return n > 64 * 512 ? n >> 9 : 64; }
+// Keys of an interval that are still ranked by counting.  Counting grows with
+// the square (64: 2 us of a row, 256: 25), another cut with the row: 300 points
+// with one far out 27 us at 64, 95 at 256; 5000 with one far out 319 us at 128,
+// 412 at 64; a mixture of 20000 points (a hundred keys in many intervals) 1.2 ms
+// at 256, 3.1 at 64.
+__device__ __forceinline__ int many_keys(int n) { return n <= 2048 ? 64 : n <= 8192 ? 128 : 256; }
 
 // Counts intervals one element at a time; MERGE (long rows, read again in
 // every pass): a thread's elements of one interval in a row are added at once,
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *
 // range of keys by at least 128 (2048 intervals over at most eleven lists),
 // so five serve any row; most take one or two.  1000 points of which one lies
 // far out: 42 us for all rows, 1718 by counting one long list, 76 with the
-// digits of a radix select; 5000: 412 us, 520 with the digits.
+// digits of a radix select; 5000: 319 us, 520 with the digits.
 template <int E>
 __global__ __launch_bounds__(ST_T) void k_row_stats_crowded(const float *S, int64_t ld, int32_t n, RowStats *out) {
     __shared__ BinShared bs;

@@ -58,7 +58,7 @@ def test_values_that_are_not_finite(n):
         np.testing.assert_array_equal(F.cpu().numpy()[k, [0, 1, 2, 3, 4, 5, 7, 8, 9, 10, 11]], ref)
 
 
-@pytest.mark.parametrize("n", [258, 259, 700, 1026, 2300, 5000, 8200])
+@pytest.mark.parametrize("n", [66, 67, 258, 259, 700, 1026, 2048, 2049, 2300, 5000, 8192, 8193])
 def test_rows_that_crowd(n):
     """Rows that take one to five cuts, beside each other in one call: ties at
     the ranks and between them, clusters inside clusters (each 2^-7 of the one
@@ -72,7 +72,7 @@ def test_rows_that_crowd(n):
         for j in range(1, level + 1):
             r[rng.permutation(n)[:n // (j + 1)]] = -1.5 - rng.random(n // (j + 1)) * 2.0 ** (-7 * j)
         rows.append(r)
-    for held in (255, 256, 257, 1023, 1024, 1025):
+    for held in (63, 64, 65, 127, 128, 129, 255, 256, 257, 1023, 1024, 1025):
         r = -1.0e6 * (1.0 + rng.random(n))
         r[:min(held, n)] = -rng.random(min(held, n))
         rows.append(rng.permutation(r))
