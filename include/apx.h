@@ -460,7 +460,7 @@ typedef struct {
 /*
  * ap_solve_batched -- Algorithm 1 on `count` independent instances of uneven
  * size (inst: host array).  Instances of up to 3072 points run in one
- * launch per class of sizes (up to 1024 points, above) with their
+ * launch per class of sizes (up to 1024, 2048 and 3072 points) with their
  * messages in registers: an instance gets as many workgroups as its rows
  * need, all instances run at once where they fit the chip, else in turns
  * largest first; their results are those of ap_solve with explicit messages,

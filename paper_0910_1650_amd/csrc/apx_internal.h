@@ -265,9 +265,10 @@ int res_max_rows(int64_t n);
 struct ResTask {
     int32_t inst, rank;
 };
-// A batch holds instances of one class only (res_small or not).
-bool res_small(int64_t n);
-hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
+// A batch holds instances of one class of sizes only (1024 points to a class).
+constexpr int kResClasses = 3;
+int res_class(int64_t n);
+hipError_t launch_resident_batch(int cls, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
                                  const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
                                  int32_t conv_iter, int32_t give_up, hipStream_t s);
 // Carves the exchange words of an instance from mem (pl.words words).

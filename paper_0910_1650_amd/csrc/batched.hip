@@ -695,7 +695,7 @@ struct ResBatch {
     std::vector<ResTask> tasks;
     std::vector<int32_t> lane;     // grid + 1 entries
     std::vector<size_t> o_x, o_e;  // exchange words (relative to o_x0), flags
-    bool small = false;            // res_small of all of them
+    int cls = 0;                   // res_class of all of them
     int grid = 0;
     size_t lds = 0;
     size_t o_tab, tab_bytes, o_task, o_lane, o_x0, x_bytes, o_out, o_abort, bytes;
@@ -707,7 +707,7 @@ struct ResBatch {
 // hold, so that the instances take the fewest turns.
 bool res_batch_plan(const BatchSpec *spec, const std::vector<int32_t> &order, int num_cus, ResBatch *B) {
     if (order.empty()) return false;
-    B->small = res_small(spec[order[0]].n);
+    B->cls = res_class(spec[order[0]].n);
     B->order = order;
     B->plan.resize(order.size());
     for (int rpw = 1; rpw <= 8; ++rpw) {
@@ -761,11 +761,11 @@ bool res_batch_plan(const BatchSpec *spec, const std::vector<int32_t> &order, in
     return true;
 }
 
-// The instances of one class (res_small or not), largest first.
-std::vector<int32_t> res_order(int32_t count, const BatchSpec *spec, bool small) {
+// The instances of one class of sizes, largest first.
+std::vector<int32_t> res_order(int32_t count, const BatchSpec *spec, int cls) {
     std::vector<int32_t> order;
     for (int32_t j = 0; j < count; ++j)
-        if (spec[j].n <= kResMaxN && res_small(spec[j].n) == small) order.push_back(j);
+        if (spec[j].n <= kResMaxN && res_class(spec[j].n) == cls) order.push_back(j);
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return spec[x].n > spec[y].n; });
     return order;
 }
@@ -804,7 +804,7 @@ apx_status res_batch_solve(apx_ctx *ctx, const ResBatch &B, const BatchSpec *spe
     const CuHold hold(ctx->device, s, B.grid, ctx->num_cus);
     if ((e = hipMemcpyAsync(b, tab.data(), B.tab_bytes, hipMemcpyHostToDevice, s)) ||
         (e = launch_res_zero(b + B.o_out, (int64_t)((B.o_x0 - B.o_out + B.x_bytes) / 8), s)) ||
-        (e = launch_resident_batch(B.small, B.grid, B.lds, reinterpret_cast<const ResInst *>(b + B.o_tab),
+        (e = launch_resident_batch(B.cls, B.grid, B.lds, reinterpret_cast<const ResInst *>(b + B.o_tab),
                                    reinterpret_cast<const ResTask *>(b + B.o_task),
                                    reinterpret_cast<const int32_t *>(b + B.o_lane),
                                    reinterpret_cast<unsigned long long *>(b + B.o_abort), params->damping,
@@ -851,9 +851,9 @@ size_t batched_ws_bytes(int32_t count, const BatchSpec *spec, int num_cus) {
         const size_t r = make_plan((int32_t)rest.size(), rest.data(), num_cus, kMaxWpc, 1).bytes;
         bytes = r > bytes ? r : bytes;
     }
-    for (bool small : {false, true}) {
+    for (int c = 0; c < kResClasses; ++c) {
         ResBatch B;
-        if (res_batch_plan(spec, res_order(count, spec, small), num_cus, &B) && B.bytes > bytes) bytes = B.bytes;
+        if (res_batch_plan(spec, res_order(count, spec, c), num_cus, &B) && B.bytes > bytes) bytes = B.bytes;
     }
     return bytes;
 }
@@ -913,10 +913,10 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
     const bool fixed = ctx->ws_external || ctx->ws_base > 0;
     ctx->last_fallback = 0;
     std::vector<char> done(count, 0);
-    ResBatch cls[2];
-    bool use[2];
-    for (int c = 0; c < 2; ++c) {
-        use[c] = !streamed && res_batch_plan(spec, res_order(count, spec, c == 1), ctx->num_cus, &cls[c]) &&
+    ResBatch cls[kResClasses];
+    bool use[kResClasses];
+    for (int c = 0; c < kResClasses; ++c) {
+        use[c] = !streamed && res_batch_plan(spec, res_order(count, spec, c), ctx->num_cus, &cls[c]) &&
                  !(fixed && ctx->ws_base + cls[c].bytes > ctx->ws_bytes);
         if (use[c])
             for (int32_t j : cls[c].order) done[j] = 1;
@@ -940,12 +940,12 @@ apx_status batched_solve(apx_ctx *ctx, int32_t count, const BatchSpec *spec, int
         const apx_status st = stream_plan(ctx, (int32_t)rest.size(), rest.data(), &P);
         if (st != APX_OK) return st;
     }
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < kResClasses; ++c)
         if (use[c]) {
             const apx_status st = ws_reserve(ctx, ctx->ws_base + cls[c].bytes);
             if (st != APX_OK) return st;
         }
-    for (int c = 0; c < 2; ++c) {
+    for (int c = kResClasses - 1; c >= 0; --c) {
         if (!use[c]) continue;
         for (int32_t j : cls[c].order) done[j] = 0;
         const apx_status st = res_batch_solve(ctx, cls[c], spec, warm, params, res, done.data());

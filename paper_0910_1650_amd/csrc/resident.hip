@@ -43,14 +43,20 @@ namespace apx {
 namespace {
 
 constexpr float kNegInf = -INFINITY;
-// (chunks, rows per wavefront) instantiated; the register file holds 12
-// chunks of three matrices per lane.  A batch launches the sets SMALL and
-// LARGE apart: one kernel with all of them spilled 228 registers.
-#define APX_RES_SMALL(X) \
+// (chunks, rows per wavefront) instantiated.  The 168 registers of a lane hold
+// eight chunks of three matrices without a spill; above, chunks of S lie in LDS
+// (below) and 12, 36, 48 and 100 bytes per lane (9 to 12 chunks) still go
+// through scratch.  The variants of a batch's kernel share one allocation, so a
+// batch launches three classes of sizes apart: 1 to 4, 5 to 8 and 9 to 12
+// chunks (20, 0 and 168 bytes; with the two upper ones in one kernel, its
+// tables in vector registers, 444: 16 instances of 1500 points 7.6 ms, 7.1
+// now, 4 of 2800 5.76 and 5.46).
+#define APX_RES_CLASS0(X) \
     X(1, 1) X(1, 2) X(1, 3) X(1, 5) X(2, 1) X(2, 2) X(2, 3) X(3, 1) X(3, 2) X(4, 1) X(4, 2)
-#define APX_RES_LARGE(X) X(5, 1) X(6, 1) X(7, 1) X(8, 1) X(9, 1) X(10, 1) X(11, 1) X(12, 1)
-#define APX_RES_VARIANTS(X) APX_RES_SMALL(X) APX_RES_LARGE(X)
-constexpr int kSmallChunks = 4;
+#define APX_RES_CLASS1(X) X(5, 1) X(6, 1) X(7, 1) X(8, 1)
+#define APX_RES_CLASS2(X) X(9, 1) X(10, 1) X(11, 1) X(12, 1)
+#define APX_RES_VARIANTS(X) APX_RES_CLASS0(X) APX_RES_CLASS1(X) APX_RES_CLASS2(X)
+constexpr int kClassChunks = 4;
 
 constexpr int RW = kResWaves;     // wavefronts per workgroup (3 per SIMD: 168 registers)
 constexpr int RT = 64 * RW;
@@ -167,8 +173,8 @@ __device__ __forceinline__ int group_of(int k, int n, int G) {
 
 // Above 9 chunks the registers do not hold all three matrices: max(0, r) is
 // then summed in two parts of the columns, and the LDS freed holds chunks of
-// S (at 12 chunks six; without it 72 registers spilled and an iteration at
-// n = 3001 took 21 us).
+// S (at 12 chunks six: 44 registers spill; without it 72, and an iteration at
+// n = 3001 took 21 us instead of 13.5).
 constexpr int res_s_chunks(int ej) { return ej <= 9 ? 0 : ej == 10 ? 3 : 6; }
 constexpr int res_parts(int ej) { return ej <= 9 ? 1 : 2; }
 
@@ -184,6 +190,8 @@ struct ResLds {
     int *e;           // exemplar flags of the member's rows
     int *cnt;         // [2][2]: exemplars, changed flags
     int *fail;
+    uint32_t *limit;  // polls of the exchanges' waits, and the iteration that gives them
+    int *give_up;     // up (not in registers: the rows need them)
 };
 
 struct ResArgs {
@@ -208,7 +216,11 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
     constexpr int NH = res_parts(EJ);         // parts of max(0, r)
     constexpr int HC = (EJ + NH - 1) / NH;    // chunks of a part
     constexpr int PC = 256 * HC;              // columns of a part
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (opaque: what follows from the thread's index would be held across a
+    // batch's instances, beside the rows)
+    int tid0 = (int)threadIdx.x;
+    opaque(tid0);
+    const int tid = tid0, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = d.n, G = d.groups, M = d.members;
     const int g0 = rank * d.gpm;
     const int g1 = g0 + d.gpm < G ? g0 + d.gpm : G;
@@ -223,6 +235,8 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
     L.e = reinterpret_cast<int *>(L.rdiag + kMaxRows);
     L.cnt = L.e + kMaxRows;
     L.fail = L.cnt + 4;
+    L.limit = reinterpret_cast<uint32_t *>(L.fail + 1);
+    L.give_up = L.fail + 2;
     L.pos = reinterpret_cast<float *>(lds + tw + 3 * 4 * kMaxRows + 32);
     L.s = L.pos + rows * PC;
 
@@ -318,15 +332,17 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         L.c[k] = 0.0f;
     }
     if (tid < 4) L.cnt[tid] = 0;
-    if (tid == 0) *L.fail = 0;
+    if (tid == 0) {
+        *L.fail = 0;
+        *L.limit = kMeetLimit;
+        *L.give_up = p.give_up;
+    }
     uint32_t eprev = 0u;   // flags of this thread's columns in the last iteration
     int run = 0;
     const float lam = p.lam, oml = 1.0f - lam;
     float lu = p.lam0, lo = 1.0f - p.lam0;    // damping of the next responsibility step
     float la = 1.0f, oa = 0.0f;               // ... availability step: A_0 stays as it is at t = 0
     bool converged = false;
-    uint32_t limit = kMeetLimit;              // polls of the waits of the exchanges
-    const int give_up = p.give_up;
     int t = 0;
     __syncthreads();
 
@@ -560,7 +576,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
 #pragma unroll
                         for (int x = 0; x < 4; ++x) off |= w[x] ^ sign;
                         if ((long long)off >= 0) break;
-                        if (++polls > limit) {
+                        if (++polls > *L.limit) {
                             bad = true;
                             break;
                         }
@@ -602,7 +618,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
                 for (int u = 0; u < NU; ++u)
                     if (tid + u * RT < n) ready &= (uint32_t)(w[u] >> 33) == (uint32_t)(t + 1);
                 if (ready) break;
-                if (++polls > limit) {
+                if (++polls > *L.limit) {
                     *L.fail = 1;
                     break;
                 }
@@ -628,10 +644,10 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
             if (enow != eprev) L.cnt[nu] = 1;
             eprev = enow;
         }
-        limit = kPollLimit;
         if (tid == 0) {
             L.cnt[nu ^ 1] = 0;
-            if (M > 1 && t == give_up) *L.fail = 1;
+            if (M > 1 && t == *L.give_up) *L.fail = 1;
+            if (first) *L.limit = kPollLimit;
         }
         __syncthreads();
         if (*L.fail) return false;
@@ -694,7 +710,7 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
         for (int k = tid; k < n; k += RT) L.t[k] = L.e[k] ? 0.0f : kNegInf;
     }
     for (int k = n + tid; k < NC; k += RT) L.t[k] = kNegInf;
-    if (M > 1 && give_up == kGiveUpAtEnd) *L.fail = 1;
+    if (M > 1 && *L.give_up == kGiveUpAtEnd) *L.fail = 1;
     __syncthreads();
     if (*L.fail) {
         if (tid == 0) d.out->wrote = 1;
@@ -795,6 +811,20 @@ __device__ __forceinline__ bool res_run(const ResInst &d, int rank, const ResArg
     return true;
 }
 
+// A value that is the same in all lanes, in scalar registers (a batch reads its
+// tables with vector loads: the rows need those registers).
+template <class V>
+__device__ __forceinline__ V scalar(const V &x) {
+    struct Words {
+        int w[sizeof(V) / 4];
+    };
+    static_assert(sizeof(Words) == sizeof(V), "whole words");
+    Words a = __builtin_bit_cast(Words, x);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(V) / 4); ++i) a.w[i] = __builtin_amdgcn_readfirstlane(a.w[i]);
+    return __builtin_bit_cast(V, a);
+}
+
 template <int EJ, int RPW>
 __global__ __launch_bounds__(RT) void k_resident(ResArgs p) {
     extern __shared__ char lds[];
@@ -853,25 +883,30 @@ __device__ __forceinline__ bool grid_met(const ResArgs &p, char *lds) {
 // Many instances of uneven size: workgroup b runs its tasks in turn.  The
 // tasks of every workgroup are in one order of the instances, so the first
 // instance not yet done always has all of its members at work on it.
-template <bool SMALL>
+template <int CLASS>
 __global__ __launch_bounds__(RT) void k_resident_batch(ResArgs p) {
     extern __shared__ char lds[];
     const int q1 = p.lane[blockIdx.x + 1];
     if (!grid_met(p, lds)) return;
     for (int q = p.lane[blockIdx.x]; q < q1; ++q) {
-        const ResTask tk = p.tasks[q];
-        const ResInst d = p.insts[tk.inst];
+        const ResTask tk = scalar(p.tasks[q]);
+        const ResInst d = scalar(p.insts[tk.inst]);
         bool ok = false;
         if (d.members > 1 && !all_arrived(d, tk.rank, p.abort, lds)) return;
 #define APX_RES_CASE(e, w) case e * 16 + w: ok = res_run<e, w>(d, tk.rank, p, lds); break;
-        if constexpr (SMALL) {
+        if constexpr (CLASS == 0) {
             switch (d.variant) {
-                APX_RES_SMALL(APX_RES_CASE)
+                APX_RES_CLASS0(APX_RES_CASE)
+            default: break;
+            }
+        } else if constexpr (CLASS == 1) {
+            switch (d.variant) {
+                APX_RES_CLASS1(APX_RES_CASE)
             default: break;
             }
         } else {
             switch (d.variant) {
-                APX_RES_LARGE(APX_RES_CASE)
+                APX_RES_CLASS2(APX_RES_CASE)
             default: break;
             }
         }
@@ -973,9 +1008,10 @@ int res_max_rows(int64_t n) {
     return most * RW;
 }
 
-bool res_small(int64_t n) { return n <= 256 * kSmallChunks; }
+int res_class(int64_t n) { return (int)((n - 1) / (256 * kClassChunks)); }
+static_assert(kResMaxN == kResClasses * 256 * kClassChunks, "classes");
 
-hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
+hipError_t launch_resident_batch(int cls, int grid, size_t lds, const ResInst *insts, const ResTask *tasks,
                                  const int32_t *lane, unsigned long long *abort, float lam, int32_t max_iter,
                                  int32_t conv_iter, int32_t give_up, hipStream_t s) {
     ResArgs a{};
@@ -988,8 +1024,9 @@ hipError_t launch_resident_batch(bool small, int grid, size_t lds, const ResInst
     a.max_iter = max_iter;
     a.conv_iter = conv_iter;
     // (a plain launch; see CuHold)
-    const void *f = small ? reinterpret_cast<const void *>(&k_resident_batch<true>)
-                          : reinterpret_cast<const void *>(&k_resident_batch<false>);
+    const void *f = cls == 0   ? reinterpret_cast<const void *>(&k_resident_batch<0>)
+                    : cls == 1 ? reinterpret_cast<const void *>(&k_resident_batch<1>)
+                               : reinterpret_cast<const void *>(&k_resident_batch<2>);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     void *args[] = {&a};

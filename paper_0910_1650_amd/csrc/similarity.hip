@@ -763,6 +763,7 @@ __global__ __launch_bounds__(SMP_T) void k_sel_sample(const float *X, int64_t n,
         }
         __syncthreads();
         crowded = held[0] > kEdgeMany || held[1] > kEdgeMany;
+        __syncthreads();                      // (held is used again below)
     }
     uint32_t end[2] = {0u, 0u};
     if (crowded) {

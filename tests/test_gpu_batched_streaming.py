@@ -1,4 +1,5 @@
-"""The streaming batched launch: the tuned plan of a batch whose small
+"""The batched launches: instances at the edges of their classes of sizes, the
+tuned plan of a batch whose small
 instances go elsewhere, and the launch's own scheduling at sizes that now run
 in registers (forced here with APX_BATCH_WPC).
 """
@@ -69,3 +70,19 @@ def test_teams_at_small_sizes(sizes, monkeypatch):
         ref = oracle.ap(S.cpu().numpy().astype(np.float64), 0.9, 400, 15)
         assert r.iterations == ref.iterations and r.converged == ref.converged
         assert np.array_equal(idx.cpu().numpy(), ref.idx)
+
+
+def test_edges_of_the_classes():
+    """Instances at the limits of the register launches and beyond, in one call:
+    each as ap_solve gives it (the streamed one to rounding)."""
+    sizes = [2048, 1024, 3072, 2049, 1025, 3073, 2]
+    Ss = [_s(n) if n > 2 else apx.to_matrix(torch.tensor([[-0.5, -1.0], [-1.5, -0.25]])) for n in sizes]
+    idx, R, A, res = _solve(Ss)
+    for j, n in enumerate(sizes):
+        r, a = apx.empty_matrix(n), apx.empty_matrix(n)
+        one, out = apx.ap_solve(Ss[j], r, a, 0.9, 40, 0)
+        assert torch.equal(idx[j], one) and res[j].n_exemplars == out.n_exemplars
+        if n <= 3072:
+            assert torch.equal(R[j], r) and torch.equal(A[j], a) and res[j] == out
+        else:
+            torch.testing.assert_close(R[j], r, rtol=0, atol=1e-4 * float(Ss[j].max() - Ss[j].min()))
