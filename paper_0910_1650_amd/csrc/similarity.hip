@@ -874,13 +874,19 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     // keys below the window and in it: lane s of every wavefront has list s
     static_assert(kSegs == 64, "a list per lane");
     unsigned long long below = segs[lane].below, total = segs[lane].count;
-    unsigned long long at_lo = segs[lane].at[0], at_hi = segs[lane].at[1];
+    unsigned long long at_lo = 0ull, at_hi = 0ull;
+    if (cut != CUT_WHOLE && win->ties) {
+        at_lo = segs[lane].at[0];
+        at_hi = segs[lane].at[1];
+        for (int off = 32; off >= 1; off >>= 1) {
+            at_lo += __shfl_xor(at_lo, off, 64);
+            at_hi += __shfl_xor(at_hi, off, 64);
+        }
+    }
     const bool over = __any(segs[lane].count > cap);
     for (int off = 32; off >= 1; off >>= 1) {
         below += __shfl_xor(below, off, 64);
         total += __shfl_xor(total, off, 64);
-        at_lo += __shfl_xor(at_lo, off, 64);
-        at_hi += __shfl_xor(at_hi, off, 64);
     }
     constexpr int PER = kWinBins / RANK_T;
     uint32_t c[PER], own = 0u;
@@ -898,8 +904,14 @@ __global__ __launch_bounds__(RANK_T) void k_win_count(SelState *st, SelWin *win,
     __syncthreads();
     for (int w = 0; w < wave; ++w) incl += wtot[w];
     const uint32_t before = incl - own;
-    const uint32_t in_bin[2] = {win->bin[0], win->bin[1]}, in_rank[2] = {win->rank[0], win->rank[1]};
-    __syncthreads();                         // (they are rewritten below)
+    uint32_t in_bin[2] = {0u, 0u}, in_rank[2] = {0u, 0u};
+    if (cut == CUT_AGAIN) {
+        for (int r = 0; r < 2; ++r) {
+            in_bin[r] = win->bin[r];
+            in_rank[r] = win->rank[r];
+        }
+        __syncthreads();                     // (they are rewritten below)
+    }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         // in ascending order: below the window, equal to its lower end, set
@@ -1097,10 +1109,12 @@ __global__ __launch_bounds__(RANK_T) void k_win_rank(SelState *st, SelWin *win, 
     for (int r = 0; r < 2; ++r) {
         uint32_t prefix = r ? b1 : b0, rank = win->rank[r];
         if (prefix == kNoBin) continue;
-        const uint32_t least = ld_dev(&win->kmin[r]);
-        if (least == ld_dev(&win->kmax[r])) {    // one value
-            if (tid == 0) st->prefix[r] = least;
-            continue;
+        if (nl > 1024u) {                        // one value only?
+            const uint32_t least = ld_dev(&win->kmin[r]);
+            if (least == ld_dev(&win->kmax[r])) {
+                if (tid == 0) st->prefix[r] = least;
+                continue;
+            }
         }
         for (int left = (int)shift; left > 0;) {
             const int bits = left < 10 ? left : 10;
