@@ -74,9 +74,10 @@ __global__ __launch_bounds__(256) void k_sqnorm(const float *X, int64_t n, int64
 
 // ---- the median's window ---------------------------------------------------
 // At n = 20000 (2e8 upper entries) about 1.7% of the keys are set aside; the
-// sample takes 20 us, counting and ranking them 30 us, and the walk in the
-// tiles' epilogue 110 us of a 644 us build, in place of two passes over S
-// (204 and 216 us): the whole build 991 -> 657 us.
+// sample takes 21 us, counting and ranking them 33 us, and the walk in the
+// tiles' epilogue 110 us (GEMM 0.48 -> 0.595 ms), in place of two passes over S
+// (204 and 216 us) and a digit counted in the epilogue (40): the whole build
+// 991 -> 661 us.
 constexpr int kSegs = 64;          // lists of set-aside keys (tile t appends to list t mod kSegs)
 constexpr int kWinBins = 4096;     // intervals the window is cut into
 constexpr int kWinList = 16384;    // keys of the intervals that hold the two ranks

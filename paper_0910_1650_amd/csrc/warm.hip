@@ -377,7 +377,9 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-// E > 0: the row (n <= E * ST_T) is held in registers; 0: read again.
+// E > 0: the row (n <= E * ST_T) is held in registers; 0: read again.  (8 to 20
+// bytes per lane go through scratch from E = 4 on: the bounds are for four
+// workgroups to a compute unit, three with 16 elements.)
 template <int E>
 __global__ __launch_bounds__(ST_T, E > 8 ? 6 : 8) void k_row_stats(const float *S, int64_t ld, int32_t n, RowStats *out) {
     __shared__ BinShared bs;
@@ -930,122 +932,122 @@ __global__ __launch_bounds__(TW) void k_mlp_bwd(BwdArgs a) {
 
     const int64_t tiles = (a.count + TP - 1) / TP;
     for (int slot = blockIdx.x; slot < a.slots; slot += ONE ? a.slots : gridDim.x) {
-    float *g = a.gpart + (int64_t)slot * NPARAM;
-    v16f dw2[4], dw1 = zero16();    // dW2 rows 32 wave + ., dW1^T-tile: features x units 32 wave + .
+        float *g = a.gpart + (int64_t)slot * NPARAM;
+        v16f dw2[4], dw1 = zero16();    // dW2 rows 32 wave + ., dW1^T-tile: features x units 32 wave + .
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dw2[q] = zero16();
-    float dw3 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f;
-    double lsum = 0.0;
+        for (int q = 0; q < 4; ++q) dw2[q] = zero16();
+        float dw3 = 0.0f, db1 = 0.0f, db2 = 0.0f, db3 = 0.0f;
+        double lsum = 0.0;
 
-    const int64_t tile0 = (a.slot0 + slot) * a.per;
-    for (int64_t tile = tile0; tile < tile0 + (ONE ? 1 : a.per) && tile < tiles; ++tile) {
-        const int64_t p0 = tile * TP;
-        if (!ONE && tile != first) tile_features(a.F, a.rows, a.count, p0, lane, xa);
-        if (wave == 3) {
+        const int64_t tile0 = (a.slot0 + slot) * a.per;
+        for (int64_t tile = tile0; tile < tile0 + (ONE ? 1 : a.per) && tile < tiles; ++tile) {
+            const int64_t p0 = tile * TP;
+            if (!ONE && tile != first) tile_features(a.F, a.rows, a.count, p0, lane, xa);
+            if (wave == 3) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    sh.x[li * (NF + 1) + 8 * hi + 4 * h + e] = bf16_val((uint16_t)xa[h][e]);
-        }
-        float g1[16], g2[16];
-        tile_hidden<true>(sh.t, xa, lane, wave, g1, g2);
-        // Loss and its gradient at the outputs: w_p * Huber(y - t), delta 1
-        if (wave == 0) {
-            float d = 0.0f, wp = 0.0f, target = 0.0f;
-            const int64_t p = p0 + li;
-            if (p < a.count) {
-                const int64_t src = a.rows ? a.rows[p] : p;
-                target = a.T[src * NO + hi];
-                wp = a.w[src];
+                    for (int e = 0; e < 4; ++e)
+                        sh.x[li * (NF + 1) + 8 * hi + 4 * h + e] = bf16_val((uint16_t)xa[h][e]);
             }
-            const float y = tile_output(sh.t, lane);
-            if (p < a.count) {
-                const float e = y - target;
-                d = wp * fminf(1.0f, fmaxf(-1.0f, e));
-                const double ae = fabs((double)e);
-                lsum += (double)wp * (ae <= 1.0 ? 0.5 * (double)e * (double)e : ae - 0.5);
+            float g1[16], g2[16];
+            tile_hidden<true>(sh.t, xa, lane, wave, g1, g2);
+            // Loss and its gradient at the outputs: w_p * Huber(y - t), delta 1
+            if (wave == 0) {
+                float d = 0.0f, wp = 0.0f, target = 0.0f;
+                const int64_t p = p0 + li;
+                if (p < a.count) {
+                    const int64_t src = a.rows ? a.rows[p] : p;
+                    target = a.T[src * NO + hi];
+                    wp = a.w[src];
+                }
+                const float y = tile_output(sh.t, lane);
+                if (p < a.count) {
+                    const float e = y - target;
+                    d = wp * fminf(1.0f, fmaxf(-1.0f, e));
+                    const double ae = fabs((double)e);
+                    lsum += (double)wp * (ae <= 1.0 ? 0.5 * (double)e * (double)e : ae - 0.5);
+                }
+                sh.dy[li * NO + hi] = d;
             }
-            sh.dy[li * NO + hi] = d;
-        }
-        __syncthreads();
-        // dz2 = (W3 dy) * GELU'(z2), in the layout of the layer's output
-        {
-            const int j = 32 * wave + li;
-            const float wa = sh.t.w3[j * NO], wb = sh.t.w3[j * NO + 1];
+            __syncthreads();
+            // dz2 = (W3 dy) * GELU'(z2), in the layout of the layer's output
+            {
+                const int j = 32 * wave + li;
+                const float wa = sh.t.w3[j * NO], wb = sh.t.w3[j * NO + 1];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
+                    sh.dz[r * LDZ + j] = fmaf(wa, sh.dy[r * NO], wb * sh.dy[r * NO + 1]) * g2[v];
+                }
+            }
+            // dW3[j][o] = sum_p h2[p][j] dy[p][o]; db3
+            {
+                const int j = tid >> 1, o = tid & 1;
+#pragma unroll 8
+                for (int p = 0; p < TP; ++p) dw3 = fmaf(bf16_val(sh.t.h2[p * LW2 + j]), sh.dy[p * NO + o], dw3);
+                if (tid < NO)
+                    for (int p = 0; p < TP; ++p) db3 += sh.dy[p * NO + tid];
+            }
+            __syncthreads();
+            // dW2[i][j] = sum_p h1[p][i] dz2[p][j]; db2
+#pragma unroll 4
+            for (int ks = 0; ks < TP / 2; ++ks) {
+                const int p = 2 * ks + hi;
+                const float av = bf16_val(sh.t.h1[p * LW2 + 32 * wave + li]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    dw2[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * q + li], dw2[q], 0, 0, 0);
+            }
+            if (tid < NH)
+                for (int p = 0; p < TP; ++p) db2 += sh.dz[p * LDZ + tid];
+            // dz1[p][i] = (sum_j dz2[p][j] W2[i][j]) * GELU'(z1): two chains of K
+            v16f s0 = zero16(), s1 = zero16();
+#pragma unroll 8
+            for (int ks = 0; ks < NH / 2; ks += 2) {
+                const int j0 = 2 * ks + hi, j1 = j0 + 2;
+                s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j0],
+                                                          bf16_val(sh.t.w2t[j0 * LW2 + 32 * wave + li]), s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j1],
+                                                          bf16_val(sh.t.w2t[j1 * LW2 + 32 * wave + li]), s1, 0, 0, 0);
+            }
+            __syncthreads();
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
-                sh.dz[r * LDZ + j] = fmaf(wa, sh.dy[r * NO], wb * sh.dy[r * NO + 1]) * g2[v];
+                sh.dz[r * LDZ + 32 * wave + li] = (s0[v] + s1[v]) * g1[v];
             }
-        }
-        // dW3[j][o] = sum_p h2[p][j] dy[p][o]; db3
-        {
-            const int j = tid >> 1, o = tid & 1;
-#pragma unroll 8
-            for (int p = 0; p < TP; ++p) dw3 = fmaf(bf16_val(sh.t.h2[p * LW2 + j]), sh.dy[p * NO + o], dw3);
-            if (tid < NO)
-                for (int p = 0; p < TP; ++p) db3 += sh.dy[p * NO + tid];
-        }
-        __syncthreads();
-        // dW2[i][j] = sum_p h1[p][i] dz2[p][j]; db2
+            __syncthreads();
+            // dW1[f][i] = sum_p x[p][f] dz1[p][i] (16 of the tile's 32 rows); db1
 #pragma unroll 4
-        for (int ks = 0; ks < TP / 2; ++ks) {
-            const int p = 2 * ks + hi;
-            const float av = bf16_val(sh.t.h1[p * LW2 + 32 * wave + li]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                dw2[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * q + li], dw2[q], 0, 0, 0);
+            for (int ks = 0; ks < TP / 2; ++ks) {
+                const int p = 2 * ks + hi;
+                const float av = li < NF ? sh.x[p * (NF + 1) + (li & (NF - 1))] : 0.0f;
+                dw1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * wave + li], dw1, 0, 0, 0);
+            }
+            if (tid < NH)
+                for (int p = 0; p < TP; ++p) db1 += sh.dz[p * LDZ + tid];
+            __syncthreads();
         }
-        if (tid < NH)
-            for (int p = 0; p < TP; ++p) db2 += sh.dz[p * LDZ + tid];
-        // dz1[p][i] = (sum_j dz2[p][j] W2[i][j]) * GELU'(z1): two chains of K
-        v16f s0 = zero16(), s1 = zero16();
-#pragma unroll 8
-        for (int ks = 0; ks < NH / 2; ks += 2) {
-            const int j0 = 2 * ks + hi, j1 = j0 + 2;
-            s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j0],
-                                                      bf16_val(sh.t.w2t[j0 * LW2 + 32 * wave + li]), s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(sh.dz[li * LDZ + j1],
-                                                      bf16_val(sh.t.w2t[j1 * LW2 + 32 * wave + li]), s1, 0, 0, 0);
-        }
-        __syncthreads();
+
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
-            sh.dz[r * LDZ + 32 * wave + li] = (s0[v] + s1[v]) * g1[v];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[OFF_W2 + (32 * wave + r) * NH + 32 * q + li] = dw2[q][v];
+            if (r < NF) g[OFF_W1 + r * NH + 32 * wave + li] = dw1[v];
         }
-        __syncthreads();
-        // dW1[f][i] = sum_p x[p][f] dz1[p][i] (16 of the tile's 32 rows); db1
-#pragma unroll 4
-        for (int ks = 0; ks < TP / 2; ++ks) {
-            const int p = 2 * ks + hi;
-            const float av = li < NF ? sh.x[p * (NF + 1) + (li & (NF - 1))] : 0.0f;
-            dw1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, sh.dz[p * LDZ + 32 * wave + li], dw1, 0, 0, 0);
+        g[OFF_W3 + tid] = dw3;
+        if (tid < NH) {
+            g[OFF_B1 + tid] = db1;
+            g[OFF_B2 + tid] = db2;
         }
-        if (tid < NH)
-            for (int p = 0; p < TP; ++p) db1 += sh.dz[p * LDZ + tid];
-        __syncthreads();
-    }
-
+        if (tid < NO) g[OFF_B3 + tid] = db3;
+        if (wave == 0) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int r = 8 * (v >> 2) + 4 * hi + (v & 3);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) g[OFF_W2 + (32 * wave + r) * NH + 32 * q + li] = dw2[q][v];
-        if (r < NF) g[OFF_W1 + r * NH + 32 * wave + li] = dw1[v];
-    }
-    g[OFF_W3 + tid] = dw3;
-    if (tid < NH) {
-        g[OFF_B1 + tid] = db1;
-        g[OFF_B2 + tid] = db2;
-    }
-    if (tid < NO) g[OFF_B3 + tid] = db3;
-    if (wave == 0) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
-        if (lane == 0) a.lpart[slot] = lsum;
-    }
+            for (int off = 32; off > 0; off >>= 1) lsum += __shfl_down(lsum, off, 64);
+            if (lane == 0) a.lpart[slot] = lsum;
+        }
     }
 }
 
@@ -1158,7 +1160,8 @@ __global__ void k_warm_a0(const float *Y, const float *sigma, int32_t n, float *
 // registers over all its rows.  The largest a + s takes the second largest
 // value; under a tie the two are equal, so comparing values names it.  Reads
 // S, writes A and R: 12 bytes per element (5000 points 54 us, 5.5 TB/s; A_0, R = 0 and
-// the general responsibility pass took 149 us and 24 bytes).
+// the general responsibility pass took 149 us and 24 bytes).  Above 16384 points
+// 68 and above 32768 points 224 bytes per lane go through scratch.
 template <int T, int J>
 __global__ __launch_bounds__(T) void k_warm_start(const float *S, const float *Y, const float *sigma, int32_t n,
                                                   int64_t ld, float *A, float *R) {
